@@ -712,6 +712,43 @@ __device__ __forceinline__ void abt_store_staged(const typename C::AccV (&acc)[C
     }
 }
 
+// acc += A B^T over K for the tile at (m0, n0); smem holds two buffers of A
+// rows, then two of B rows.
+template <typename T, class C, bool MIS>
+__device__ __forceinline__ void abt_products(const T* __restrict__ Asrc, int64_t lda, int64_t m0, int64_t M,
+                                             int64_t Ka, const T* __restrict__ Bsrc, int64_t ldb, int64_t n0,
+                                             int64_t N, int64_t Kb, int64_t K, T* smem,
+                                             typename C::AccV (&acc)[C::FN][C::FM], int wm, int wn, int lane,
+                                             int tid) {
+    constexpr int kAs = C::BM * C::LDK, kBs = C::BN * C::LDK;
+    const int nfm = live_frags<C::FM>(m0 + wm * C::WTM, M), nfn = live_frags<C::FN>(n0 + wn * C::WTN, N);
+    using TA = KTile<C, C::BM, T, MIS>;
+    using TB = KTile<C, C::BN, T>;   // T'^T (or the certificate's factors): aligned rows
+    const typename TA::Geo ga = TA::geo(Asrc, lda, m0, M, tid, Asrc + (M - 1) * lda + (Ka - 1));
+    const typename TB::Geo gb = TB::geo(Bsrc, ldb, n0, N, tid);
+    TA ta[2];
+    TB tb[2];
+    const int nsteps = (int)((K + C::BK - 1) / C::BK);
+    by_edge(nfm == C::FM && nfn == C::FN, [&](auto edge) {
+        pipeline2<kPeelAbt<T, MIS>>(
+            nsteps, (int)(std::min(std::min(Ka, Kb), K) / C::BK),
+            [&](int st, int j, auto in) {
+                const int64_t k0 = (int64_t)j * C::BK;
+                ta[st].fetch(ga, k0, !decltype(in)::value && k0 + C::BK > Ka, Ka);
+                tb[st].fetch(gb, k0, !decltype(in)::value && k0 + C::BK > Kb, Kb);
+            },
+            [&](int st, int buf, int j, auto in) {
+                const int64_t k0 = (int64_t)j * C::BK;
+                ta[st].stash(smem + buf * kAs, ga, k0, !decltype(in)::value && k0 + C::BK > Ka, Ka);
+                tb[st].stash(smem + 2 * kAs + buf * kBs, gb, k0, !decltype(in)::value && k0 + C::BK > Kb, Kb);
+            },
+            [&](int buf) {
+                mma_k_g<C, decltype(edge)::value>(smem + buf * kAs, smem + 2 * kAs + buf * kBs, acc, wm, wn, lane,
+                                                   nfm, nfn);
+            });
+    });
+}
+
 // C[m][n] = sum_k A[m][k] B[n][k]  (both sources with K contiguous).
 // One workgroup per tile, in the order of AbtOrder.
 //   ABT_STORE: Y[m][ldy] = C rounded to T.
@@ -739,7 +776,6 @@ __global__ __launch_bounds__(C::NT, (kAbtMinWaves<T, MIS>)) void k_abt(
     if (nt >= tiles_n) return;
     const int64_t tile = mt * tiles_n + nt;
     const int64_t m0 = mt * C::BM, n0 = nt * C::BN;
-    const int nfm = live_frags<C::FM>(m0 + wm * C::WTM, M), nfn = live_frags<C::FN>(n0 + wn * C::WTN, N);
 
     AccV acc[C::FN][C::FM];
 #pragma unroll
@@ -747,31 +783,7 @@ __global__ __launch_bounds__(C::NT, (kAbtMinWaves<T, MIS>)) void k_abt(
 #pragma unroll
         for (int fm = 0; fm < C::FM; ++fm) acc[fn][fm] = zero_accv<AccV>();
 
-    using TA = KTile<C, C::BM, T, MIS>;
-    using TB = KTile<C, C::BN, T>;   // T'^T (or the certificate's factors): aligned rows
-    const typename TA::Geo ga = TA::geo(Asrc, lda, m0, M, tid, Asrc + (M - 1) * lda + (Ka - 1));
-    const typename TB::Geo gb = TB::geo(Bsrc, ldb, n0, N, tid);
-    TA ta[2];
-    TB tb[2];
-    const int nsteps = (int)((K + C::BK - 1) / C::BK);
-    by_edge(nfm == C::FM && nfn == C::FN, [&](auto edge) {
-        pipeline2<kPeelAbt<T, MIS>>(
-            nsteps, (int)(std::min(std::min(Ka, Kb), K) / C::BK),
-            [&](int st, int j, auto in) {
-                const int64_t k0 = (int64_t)j * C::BK;
-                ta[st].fetch(ga, k0, !decltype(in)::value && k0 + C::BK > Ka, Ka);
-                tb[st].fetch(gb, k0, !decltype(in)::value && k0 + C::BK > Kb, Kb);
-            },
-            [&](int st, int buf, int j, auto in) {
-                const int64_t k0 = (int64_t)j * C::BK;
-                ta[st].stash(smem + buf * kAs, ga, k0, !decltype(in)::value && k0 + C::BK > Ka, Ka);
-                tb[st].stash(smem + 2 * kAs + buf * kBs, gb, k0, !decltype(in)::value && k0 + C::BK > Kb, Kb);
-            },
-            [&](int buf) {
-                mma_k_g<C, decltype(edge)::value>(smem + buf * kAs, smem + 2 * kAs + buf * kBs, acc, wm, wn, lane,
-                                                   nfm, nfn);
-            });
-    });
+    abt_products<T, C, MIS>(Asrc, lda, m0, M, Ka, Bsrc, ldb, n0, N, Kb, K, smem, acc, wm, wn, lane, tid);
 
     const int r = lane & 15, g = lane >> 4;
     if (MODE == ABT_STORE) {
@@ -1104,6 +1116,8 @@ static bool needs_stage(const void* p, int64_t ld, int prec) {
     return (ld % vec != 0) || (reinterpret_cast<uintptr_t>(p) % 16 != 0);
 }
 
+#include "apply_split.h"
+
 // Tile edges and K step of the matrix-core configurations, for the plan (the
 // grids and the split-K partial buffers are sized from the same constants
 // the kernels are compiled with).
@@ -1122,6 +1136,10 @@ static TileDims cfg_dims(int prec, bool big) {
     if (prec == P64) return big ? dims_of<BigCfg<double>::C>() : dims_of<SmallCfg<double>::C>();
     if (prec == P32) return big ? dims_of<BigCfg<float>::C>() : dims_of<SmallCfg<float>::C>();
     return big ? dims_of<BigCfg<half_t>::C>() : dims_of<SmallCfg<half_t>::C>();
+}
+
+size_t apply_workspace_bytes(const ApplyPlan& p) {
+    return round_up(p.part_bytes, 256) + round_up(p.mid_bytes, 256) + p.stage_bytes;
 }
 
 ApplyPlan plan_apply(int64_t m, int64_t n, int64_t k, int64_t b, int prec, int path, const void* U,
@@ -1214,11 +1232,9 @@ ApplyPlan plan_apply(int64_t m, int64_t n, int64_t k, int64_t b, int prec, int p
                         (p.stage_v ? round_up((size_t)n * p.Kp * e, 256) : 0) +
                         (p.stage_x ? round_up((size_t)n * p.ldx * e, 256) : 0);
     }
+    p.scratch_bytes = apply_workspace_bytes(p);
+    if (path == 2 && !forced_tile() && x3_takes(m, n, k, b, prec, U, V, X)) x3_plan(p, m, n, k, b);
     return p;
-}
-
-size_t apply_workspace_bytes(const ApplyPlan& p) {
-    return round_up(p.part_bytes, 256) + round_up(p.mid_bytes, 256) + p.stage_bytes;
 }
 
 template <typename T> static const char* p1_stream_label();
@@ -1279,6 +1295,9 @@ static hipError_t apply_typed(const ApplyPlan& p, const T* U, const T* s, const 
         else LRC_P2S(8, false);
 #undef LRC_P2S
         return hipGetLastError();
+    }
+    if constexpr (std::is_same<T, float>::value) {
+        if (p.x3) return x3_apply(p, U, s, V, X, Y, m, n, k, b, part, Tt, ws, stream);
     }
     // operands whose pitch or base rule out 16-byte moves, unless read in place
     const T *Ug = U, *Vg = V, *Xg = X;

@@ -353,8 +353,9 @@ int lrc_matrix_apply_noalloc(const void* U, const void* s, const void* V, const 
                              int64_t n, int64_t k, int64_t batch, int prec) {
     int rc = check_apply_arrays(U, s, V, X, Y, m, n, k, batch, prec);
     if (rc) return rc;
-    const ApplyPlan plan = plan_apply(m, n, k, batch, prec, g_force_path, U, V, X);
-    const size_t need = apply_workspace_bytes(plan);
+    ApplyPlan plan = plan_apply(m, n, k, batch, prec, g_force_path, U, V, X);
+    if (plan.x3) x3_panels(plan, m, batch, (size_t)LRC_NOALLOC_SCRATCH_BYTES);
+    const size_t need = plan.scratch_bytes;
     if (need > (size_t)LRC_NOALLOC_SCRATCH_BYTES)
         return fail(LRC_EINVAL, "this apply needs %zu bytes of scratch, above the %lld of the allocation-free entry",
                     need, (long long)LRC_NOALLOC_SCRATCH_BYTES);

@@ -60,6 +60,14 @@ struct ApplyPlan {
     int mis1, mis2;
     int stage_u, stage_v, stage_x;
     int64_t ldx;
+    // FP32 by split products on the bfloat16 matrix cores (large batches): rank
+    // fragments of 16 per phase-1 tile, padded rank, pitch of the planes of U and
+    // T'^T, and panels (splits of V, batch columns, rows of U) held in scratch at
+    // a time; part_bytes, mid_bytes and stage_bytes are those of one panel
+    int x3, nf;
+    int64_t kpad, ldk;
+    int64_t vgroup, bpanel, mpanel;
+    size_t scratch_bytes;   // of the plan without the split: what the allocation-free entry is limited by
     size_t stage_bytes;
     size_t part_bytes;   // partial-sum buffer
     size_t mid_bytes;    // T'^T buffer
@@ -69,6 +77,8 @@ struct ApplyPlan {
 ApplyPlan plan_apply(int64_t m, int64_t n, int64_t k, int64_t b, int prec, int path, const void* U = nullptr,
                      const void* V = nullptr, const void* X = nullptr);
 size_t apply_workspace_bytes(const ApplyPlan& p);
+// Cuts the panels of a split plan (p.x3) to `limit` bytes of scratch.
+void x3_panels(ApplyPlan& p, int64_t m, int64_t b, size_t limit);
 
 hipError_t launch_apply(const ApplyPlan& p, const void* U, const void* s, const void* V,
                         const void* X, void* Y, int64_t m, int64_t n, int64_t k, int64_t b,

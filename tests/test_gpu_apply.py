@@ -224,3 +224,62 @@ def test_large_rank_small_batch(lrc):
     print("apply 8300x8250 k=8200 b=1 fp64", flush=True)
     Y, (u, s, v, x) = _run(lrc, U, s, V, X, "fp64")
     _assert_parity(Y, u, s, v, x, "fp64")
+
+
+# ---- FP32 by split products on the bfloat16 matrix cores (large batches) ----
+
+@pytest.mark.parametrize("m,n,k,b", [
+    (129, 8200, 97, 2049),     # one row past a tile, odd rank and batch, a short last K step
+    (4100, 4111, 17, 2047),    # two fragments, odd everything
+    (2050, 6200, 273, 2048),   # two rank tiles, the second one padded
+    (16385, 257, 256, 1025),   # few rows of V, whole K steps
+])
+def test_fp32_split_products(lrc, m, n, k, b):
+    """Edges of the split path's tiles against the oracle at the FP32
+    tolerance and the componentwise FP32 bound."""
+    d = synth.random_factors(m, n, k, b, tag=k + b)
+    print(f"apply split m={m} n={n} k={k} b={b}", flush=True)
+    Y, (u, s, v, x) = _run(lrc, d["U"], d["s"], d["V"], d["X"], "fp32")
+    _assert_parity(Y, u, s, v, x, "fp32")
+
+
+def test_fp32_split_panels_same_bits(lrc):
+    """8192 x 8192, rank 257, batch 4096: the planes and partial sums of one
+    pass (about 120 MB) exceed the allocation-free entry's scratch, which cuts
+    them to panels; every output bit agrees."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(3)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")   # noqa: E731
+    args = rnd(8192, 257) / 90, torch.rand(257, generator=g, device="cuda"), rnd(8192, 257) / 90, rnd(8192, 4096)
+    out = torch.full((8192, 4096), float("nan"), device="cuda")
+    lrc.matrix_apply_noalloc(*args, out)
+    assert torch.equal(out, lrc.matrix_apply(*args))
+
+
+@pytest.mark.parametrize("what", ["inf", "nan", "tiny", "huge"])
+def test_fp32_split_special_values(lrc, what):
+    """Values outside the split's range (2^-100 to 2^62): their tiles run on
+    the FP32 instruction, so infinities and NaN land where the FP64 product
+    has them, and tiny or huge columns keep the FP32 tolerance by themselves."""
+    m, n, k, b = 1030, 1500, 70, 8200
+    d = synth.random_factors(m, n, k, b, tag=9)
+    U, s, V, X = (np.array(d[q], dtype=np.float32) for q in ("U", "s", "V", "X"))
+    if what == "inf":
+        X[7, 5000] = np.inf
+        U[9, 3] = -np.inf
+    elif what == "nan":
+        X[1400, 17] = np.nan
+        U[1029, 69] = np.nan
+    elif what == "tiny":
+        X[:, 3000:] *= np.float32(1e-36)
+    else:
+        V[5] *= np.float32(1e30)
+        X[5] *= np.float32(1e6)
+    Y = lrc.matrix_apply(*[to_dev(a) for a in (U, s, V, X)]).cpu().numpy()
+    with np.errstate(all="ignore"):
+        ref = U.astype(np.float64) @ (s.astype(np.float64)[:, None] * (V.astype(np.float64).T @ X.astype(np.float64)))
+    assert np.array_equal(np.isnan(Y), np.isnan(ref))
+    assert np.array_equal(np.isinf(Y), np.isinf(ref))
+    for cols in (slice(0, 3000), slice(3000, b)):
+        ok = np.isfinite(ref[:, cols])
+        assert rel_fro(np.where(ok, Y[:, cols], 0), np.where(ok, ref[:, cols], 0)) <= TOL["fp32"]
