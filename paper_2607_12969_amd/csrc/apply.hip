@@ -1111,12 +1111,15 @@ static int forced_tile() {
     return t;
 }
 
+static int64_t tiles_of(int64_t n, int b) { return (n + b - 1) / b; }
+
 static bool needs_stage(const void* p, int64_t ld, int prec) {
     const int64_t vec = 16 / (int64_t)elem_bytes(prec);
     return (ld % vec != 0) || (reinterpret_cast<uintptr_t>(p) % 16 != 0);
 }
 
 #include "apply_split.h"
+#include "apply_half.h"
 
 // Tile edges and K step of the matrix-core configurations, for the plan (the
 // grids and the split-K partial buffers are sized from the same constants
@@ -1371,6 +1374,14 @@ static hipError_t apply_typed(const ApplyPlan& p, const T* U, const T* s, const 
 #define LRC_P2(CFG, MISV)                                                                                       \
     launch_abt<T, CFG, ABT_STORE, MISV>(g2, stream, Ug, ldu, m, k, (const T*)Tt, ldt, b, ldt, ldt, tm, tn, Y, b,     \
                                         vec16, (const double*)nullptr, (int64_t)0, (double*)nullptr)
+    if constexpr (std::is_same<T, half_t>::value) {
+        if (half_takes(p, m, b)) {
+            const int wm = (int)((m + HalfC2::BM - 1) / HalfC2::BM);
+            hipLaunchKernelGGL(k_p2_half, dim3(xcd_grid(AbtOrder(wm, tn).total)), dim3(256), 0, stream, Ug, ldu, m,
+                               p.stage_u ? p.Kp : k, (const half_t*)Tt, ldt, b, wm, tn, Y, b, vec16);
+            return hipGetLastError();
+        }
+    }
     if (p.big2) {
         if (p.mis2) LRC_P2(Big, true); else LRC_P2(Big, false);
     } else {
@@ -1532,8 +1543,6 @@ static void split_plan(int64_t tiles, int64_t K, int* splits, int64_t* chunk) {
     *chunk = round_up((K + sp - 1) / sp, GramC::BK);
     *splits = (int)((K + *chunk - 1) / *chunk);
 }
-
-static int64_t tiles_of(int64_t n, int b) { return (n + b - 1) / b; }
 
 // At most 96 rows of W (the factorization's sketches and small factors) take
 // one 96-row tile, three fragments per wave (75 test vectors leave 21 of 96

@@ -226,6 +226,27 @@ def test_large_rank_small_batch(lrc):
     _assert_parity(Y, u, s, v, x, "fp64")
 
 
+@pytest.mark.parametrize("m,n,k,b", [
+    (16129, 300, 8, 1024),      # one K step, mostly zero columns past k; one row in the last tile
+    (16384, 400, 33, 1032),     # copied factor, one column past a K step; eight columns in the last tile
+    (13000, 700, 104, 1283),    # aligned rank that ends inside a K step, odd batch
+    (4100, 600, 256, 4096),     # whole K steps
+])
+def test_fp16_wide_tiles(lrc, m, n, k, b):
+    """Phase 2 on 256 x 128 tiles (at least 512 of them): edges in every
+    dimension against the oracle, with a huge value past the last row's rank
+    range in the neighbouring row (columns past k must not leak)."""
+    d = synth.random_factors(m, n, k, b, tag=k + b)
+    print(f"apply wide m={m} n={n} k={k} b={b}", flush=True)
+    U = np.array(d["U"])
+    U[5, 0] = np.inf
+    Y, (u, s, v, x) = _run(lrc, U, d["s"], d["V"], d["X"], "fp16")
+    assert not np.isfinite(Y[5]).any() and np.isfinite(np.delete(Y, 5, 0)).all()
+    u[5, 0], Y[5] = 0.0, 0.0
+    Y[5] = O.apply(u[5:6], s, v, x)[0]
+    _assert_parity(Y, u, s, v, x, "fp16")
+
+
 # ---- FP32 by split products on the bfloat16 matrix cores (large batches) ----
 
 @pytest.mark.parametrize("m,n,k,b", [
