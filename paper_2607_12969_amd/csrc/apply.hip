@@ -1121,6 +1121,14 @@ static bool needs_stage(const void* p, int64_t ld, int prec) {
 #include "apply_split.h"
 #include "apply_half.h"
 
+template <typename T> static const char* p1_stream_label();
+template <typename T> static const char* p2_stream_label();
+template <typename T> static const char* p1_mfma_label();
+template <typename T> static const char* p2_mfma_label();
+template <typename T> static const char* p1_finish_label();
+
+#include "apply_small.h"
+
 // Tile edges and K step of the matrix-core configurations, for the plan (the
 // grids and the split-K partial buffers are sized from the same constants
 // the kernels are compiled with).
@@ -1236,15 +1244,17 @@ ApplyPlan plan_apply(int64_t m, int64_t n, int64_t k, int64_t b, int prec, int p
                         (p.stage_x ? round_up((size_t)n * p.ldx * e, 256) : 0);
     }
     p.scratch_bytes = apply_workspace_bytes(p);
-    if (path == 2 && !forced_tile() && x3_takes(m, n, k, b, prec, U, V, X)) x3_plan(p, m, n, k, b);
+    if (path == 2 && !forced_tile()) {
+        if (small_takes(m, n, k, b)) {
+            p.small = 1;
+            p.part_bytes = p.mid_bytes = p.stage_bytes = 0;
+        } else if (x3_takes(m, n, k, b, prec, U, V, X)) {
+            x3_plan(p, m, n, k, b);
+        }
+    }
     return p;
 }
 
-template <typename T> static const char* p1_stream_label();
-template <typename T> static const char* p2_stream_label();
-template <typename T> static const char* p1_mfma_label();
-template <typename T> static const char* p2_mfma_label();
-template <typename T> static const char* p1_finish_label();
 #define LRC_LABELS(T, S)                                                          \
     template <> const char* p1_stream_label<T>() { return "apply_p1_stream_" S; } \
     template <> const char* p2_stream_label<T>() { return "apply_p2_stream_" S; } \
@@ -1263,7 +1273,9 @@ static hipError_t apply_typed(const ApplyPlan& p, const T* U, const T* s, const 
     using Acc = typename PrecTraits<T>::acc;
     Acc* part = static_cast<Acc*>(ws.take(p.part_bytes));
     T* Tt = static_cast<T*>(ws.take(p.mid_bytes));
-    if (ws.overrun || !Tt) return hipErrorOutOfMemory;
+    if (ws.overrun) return hipErrorOutOfMemory;
+    if (p.small) return small_apply<T>(U, s, V, X, Y, m, n, k, b, stream);
+    if (!Tt) return hipErrorOutOfMemory;
     const int64_t ldt = p.Kp;
     if (p.path == 1) {
         const int nb = b <= 1 ? 1 : b <= 2 ? 2 : b <= 4 ? 4 : 8;

@@ -67,6 +67,7 @@ struct ApplyPlan {
     int x3, nf;
     int64_t kpad, ldk;
     int64_t vgroup, bpanel, mpanel;
+    int small;           // one launch for both phases (no scratch)
     size_t scratch_bytes;   // of the plan without the split: what the allocation-free entry is limited by
     size_t stage_bytes;
     size_t part_bytes;   // partial-sum buffer

@@ -226,6 +226,24 @@ def test_large_rank_small_batch(lrc):
     _assert_parity(Y, u, s, v, x, "fp64")
 
 
+@pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("m,n,k,b", [
+    (65, 9, 9, 17),         # one row and column past a tile, waves without rows
+    (512, 256, 20, 64),     # whole batches of rows
+    (130, 257, 33, 31),     # a second block of one rank index, a second batch of one row per wave
+    (500, 250, 128, 9),     # the largest rank, four blocks
+    (70, 1000, 31, 10),     # four batches
+    (2, 3, 1, 4000),        # a tiny factor and many columns
+])
+def test_one_launch_small(lrc, m, n, k, b, prec):
+    """Sizes that take the single launch: edges of its tiles, batches and
+    rank blocks against the oracle."""
+    d = synth.random_factors(m, n, k, b, tag=m + n + k + b)
+    print(f"apply small launch {prec} m={m} n={n} k={k} b={b}", flush=True)
+    Y, (u, s, v, x) = _run(lrc, d["U"], d["s"], d["V"], d["X"], prec)
+    _assert_parity(Y, u, s, v, x, prec)
+
+
 @pytest.mark.parametrize("m,n,k,b", [
     (16129, 300, 8, 1024),      # one K step, mostly zero columns past k; one row in the last tile
     (16384, 400, 33, 1032),     # copied factor, one column past a K step; eight columns in the last tile
