@@ -66,6 +66,21 @@ def test_small_shapes_match_oracle(lrc, case):
     _compare(_gauge(lrc, cores, label), cores, label)
 
 
+@pytest.mark.parametrize("rank", [15, 16, 17, 32, 33, 47, 48, 49, 64, 80, 81, 95])
+def test_every_block_count_of_the_triangular_kernels(lrc, rank):
+    """Ranks at the edges of the Cholesky's and the triangular solve's blocks of 16."""
+    dims, ranks = (rank + 3, 19, 2), (1, rank, 2, 1)
+    cores = _gaussian_cores(dims, ranks, rank)
+    _compare(_gauge(lrc, cores, f"rank {rank}"), cores, rank)
+
+
+@pytest.mark.parametrize("rows,rank", [(32767, 7), (32768, 18), (65573, 33)])
+def test_tall_unfoldings(lrc, rows, rank):
+    """Both row tilings of the triangular solve, a ragged last tile, several tiles per workgroup."""
+    cores = _gaussian_cores((rows, 3), (1, rank, 1), rows)
+    _compare(_gauge(lrc, cores, f"{rows} rows"), cores, rows)
+
+
 WORKLOADS = [
     ("cube 256^3 r15", (256, 256, 256), (1, 15, 15, 1)),
     ("six-way 16^6", (16,) * 6, (1, 9, 17, 25, 17, 9, 1)),
