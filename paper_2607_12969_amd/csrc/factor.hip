@@ -26,8 +26,6 @@
 namespace lrc {
 
 constexpr int kFactMaxL = LRC_RSVD_MAX_SAMPLES;
-constexpr int kJacThreads = 1024;
-constexpr int kJacWaves = kJacThreads / 64;
 constexpr int kJacSweeps = 40;
 
 // dst (drows x ldd) = src (rows x cols, pitch lds) with zeros past rows / cols
@@ -85,43 +83,186 @@ __device__ __forceinline__ void group16_sum3(double& a, double& b, double& c) {
     a += dpp_f64<kMirror>(a); b += dpp_f64<kMirror>(b); c += dpp_f64<kMirror>(c);
 }
 
+// Move within quads of lanes: lane i receives the value of lane i ^ X.
+template <int X>
+__device__ __forceinline__ double quad_xor(double v) {
+    return dpp_f64<X == 1 ? 0xB1 : X == 2 ? 0x4E : 0x1B>(v);
+}
+
+// Sum over the 16 lanes with equal lane & 3: rotations by 8 and 4 within
+// rows of 16 lanes, then swaps of neighbouring rows and of the wave's halves.
+// Every step adds two equal-ordered partial sums, so that the 16 lanes end
+// with identical totals.
+__device__ __forceinline__ double stride4_sum(double x) {
+    x += dpp_f64<0x128>(x);
+    x += dpp_f64<0x124>(x);
+    {
+        const long long b = __builtin_bit_cast(long long, x);
+        const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)b, (unsigned)b, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+        x = __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
+            __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+    }
+    const long long b = __builtin_bit_cast(long long, x);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)b, (unsigned)b, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(b >> 32), (unsigned)(b >> 32), false, false);
+    return __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+}
+
+// Rotation of columns p, q with al = |p|^2, be = |q|^2, ga = p . q: the
+// smaller root t = tan of t^2 + 2 zeta t - 1 = 0, zeta = (be - al) / (2 ga),
+// as t = sign(d) g / (|d| + sqrt(d^2 + g^2)) with d = be - al, g = 2 ga scaled
+// by a power of two so that the squares stay in range.  t only has to make
+// the columns orthogonal to well below the threshold (one Newton step on
+// the hardware's 2^-24 estimates, 2^-46); c = 1 / sqrt(1 + t^2) and s = c t
+// are to full precision (two steps), which keeps the rotation orthogonal.
+// Returns false and the identity where |ga| <= tol |p| |q|.  flip: sign of
+// t when d = 0.
+__device__ __forceinline__ bool jac_rotation(double al, double be, double ga, double tol, bool flip, double& t,
+                                             double& c, double& s) {
+    const double cosine = __builtin_fabs(ga) * __builtin_amdgcn_rsq(al) * __builtin_amdgcn_rsq(be);
+    const bool rot = ga != 0.0 && cosine > tol;
+    const int e = -__builtin_amdgcn_frexp_exp(__builtin_fmax(al, be));
+    const double d = __builtin_amdgcn_ldexp(be - al, e), g = __builtin_amdgcn_ldexp(ga, e + 1);
+    const double h2 = d * d + g * g;
+    double y = __builtin_amdgcn_rsq(h2);
+    y = __builtin_fma(0.5 * y, __builtin_fma(-h2 * y, y, 1.0), y);
+    const double w = __builtin_fabs(d) + h2 * y;
+    double z = __builtin_amdgcn_rcp(w);
+    z = __builtin_fma(z, __builtin_fma(-w, z, 1.0), z);
+    t = (d < 0.0 || (d == 0.0 && flip)) ? -(g * z) : g * z;
+    t = rot ? t : 0.0;
+    const double u = __builtin_fma(t, t, 1.0);
+    c = __builtin_amdgcn_rsq(u);
+    c = __builtin_fma(0.5 * c, __builtin_fma(-u * c, c, 1.0), c);
+    c = __builtin_fma(0.5 * c, __builtin_fma(-u * c, c, 1.0), c);
+    c = rot ? c : 1.0;
+    s = c * t;
+    return rot;
+}
+
+// A column's share of a lane: entries e0 + 16 u of m_j and of z_j, and |m_j|^2.
+template <int PER>
+struct JacCol {
+    double m[PER], z[PER], nn;
+    __device__ __forceinline__ void load(const double* mc, const double* jc) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            m[u] = mc[16 * u];
+            z[u] = jc[16 * u];
+        }
+        nn = stride4_sum(dot(*this));
+    }
+    __device__ __forceinline__ void store(double* mc, double* jc) const {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            mc[16 * u] = m[u];
+            jc[16 * u] = z[u];
+        }
+    }
+    __device__ __forceinline__ double dot(const JacCol& o) const {
+        double x = 0.0;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) x = __builtin_fma(m[u], o.m[u], x);
+        return x;
+    }
+    template <int X>
+    __device__ __forceinline__ JacCol moved() const {
+        JacCol r;
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            r.m[u] = quad_xor<X>(m[u]);
+            r.z[u] = quad_xor<X>(z[u]);
+        }
+        r.nn = quad_xor<X>(nn);
+        return r;
+    }
+    // this = c this + s o
+    __device__ __forceinline__ void combine(double c, double s, const JacCol& o) {
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            m[u] = c * m[u] + s * o.m[u];
+            z[u] = c * z[u] + s * o.z[u];
+        }
+    }
+};
+
+// Pair (a, b) of a lane's quarter of the wave, a before b.
+template <int PER>
+__device__ __forceinline__ bool jac_cross(JacCol<PER>& a, JacCol<PER>& b, double tol) {
+    double t, c, s;
+    const double ga = stride4_sum(a.dot(b));
+    const bool rot = jac_rotation(a.nn, b.nn, ga, tol, false, t, c, s);
+    if (__builtin_amdgcn_ballot_w64(rot) == 0) return false;
+    const JacCol<PER> a0 = a;
+    a.combine(c, -s, b);
+    b.combine(c, s, a0);
+    a.nn = __builtin_fma(-t, ga, a.nn);
+    b.nn = __builtin_fma(t, ga, b.nn);
+    return true;
+}
+
+// Pairs of the columns of one block, (q, q ^ X) for q = lane & 3: both lanes
+// of a pair form the same rotation and update their own column.
+template <int PER, int X>
+__device__ __forceinline__ bool jac_inside(JacCol<PER>& a, bool second, double tol) {
+    double t, c, s;
+    const JacCol<PER> o = a.template moved<X>();
+    const double ga = stride4_sum(a.dot(o));
+    const bool rot = jac_rotation(a.nn, o.nn, ga, tol, second, t, c, s);
+    if (__builtin_amdgcn_ballot_w64(rot) == 0) return false;
+    a.combine(c, -s, o);
+    a.nn = __builtin_fma(-t, ga, a.nn);
+    return true;
+}
+
 // One workgroup: SVD of M = R^T (R upper triangular, l x l inside pitch ldr)
 // by one-sided (Hestenes) Jacobi.  The columns of M (rows of R) and of the
 // accumulated rotation Z sit in LDS, the columns first put in non-increasing
-// order of their norms (de Rijk's ordering); a sweep visits every column pair once
-// in l' - 1 rounds of the round-robin (circle) ordering, l' = l rounded up to
-// even.  The l'/2 <= 48 disjoint pairs of a round run at once, one per
-// group of 16 lanes (64 groups), each lane holding entries e = lane + 16 u
-// of the two columns.  A pair (p, q) is rotated when |m_p . m_q| > tol
-// ||m_p|| ||m_q||, tol = max(l, 8) 2^-53, by the rotation that makes the two
-// columns orthogonal (the smaller root of t^2 + 2 zeta t - 1 = 0, zeta =
-// (|m_q|^2 - |m_p|^2) / (2 m_p . m_q)).  The sweeps stop when one rotates
-// nothing; *flag = 1 if 40 sweeps do not get there.  Then sigma_j = ||m_j||,
+// order of their norms (de Rijk's ordering).  A pair (p, q) is rotated when
+// |m_p . m_q| > tol ||m_p|| ||m_q||, tol = max(l, 8) 2^-53, by the rotation
+// that makes the two columns orthogonal.  A sweep visits every pair once,
+// by blocks of four columns: in each of nb - 1 rounds of the round-robin
+// (circle) ordering of the nb blocks (rounded up to even; columns past l are
+// zero) a wave takes two blocks into registers, four columns of each on the
+// four residues of lane & 3, rotates the 16 pairs across them in four steps
+// (the second block moves one residue on within quads), and puts them back;
+// one barrier per round.  Round 0 begins with the pairs inside the blocks.
+// Norms are summed when a block is loaded and updated by its rotations.  The
+// sweeps stop when one rotates nothing (all its norms are then the summed
+// ones); *flag = 1 if 40 sweeps do not get there.  Then sigma_j = ||m_j||,
 // and the columns are written in non-increasing order of sigma (ties by
 // index): sv[pos] = sigma, Wt[pos][:] = m_j / sigma_j (zero when sigma_j =
 // 0), Zt[pos][:] = z_j, and, when Zts is not null, Zts[pos][:] = sigma_j z_j;
 // rows of pitch ldw with zeros in columns l..ldw-1; s_out[pos] = sigma for
 // pos < k when not null.
-constexpr int kJacPer = kFactMaxL / 16;   // entries of a column per lane
-static_assert(kFactMaxL % 16 == 0 && kFactMaxL / 2 <= kJacThreads / 16, "one group of 16 lanes per pair");
+// Bound by the issue of one compute unit and the chain dot - rotation -
+// update of a step, about 8 (4 ceil(l / 8) + 1) steps; a round per column
+// pair, with IEEE divisions and a trip through LDS each, took 1006 us at l = 74,
+// this takes 652.
+constexpr int kJacPitch = 104;   // doubles: four neighbouring columns fall on distinct banks
+constexpr int kJacThreads = 64 * (kFactMaxL / 8);
+static_assert(kFactMaxL % 16 == 0 && kFactMaxL <= kJacPitch, "blocks of the largest sketch");
+template <int PER>
 __global__ __launch_bounds__(kJacThreads) void k_fact_jacobi(const double* __restrict__ R, int l, int ldr, int k,
                                                              double* __restrict__ sv, double* __restrict__ s_out,
                                                              double* __restrict__ Wt, double* __restrict__ Zt,
                                                              double* __restrict__ Zts, int ldw, int* __restrict__ flag) {
-    __shared__ double Mc[kFactMaxL][kFactMaxL + 1];
-    __shared__ double Jc[kFactMaxL][kFactMaxL + 1];
-    __shared__ double sig[kFactMaxL];
-    __shared__ int pos[kFactMaxL];
-    __shared__ int rotated;
-    const int tid = threadIdx.x;
+    __shared__ double Mc[16 * PER][kJacPitch];
+    __shared__ double Jc[16 * PER][kJacPitch];
+    __shared__ double sig[16 * PER];
+    __shared__ int pos[16 * PER];
+    __shared__ int rotated[kJacSweeps];
+    const int tid = threadIdx.x, nth = blockDim.x;
     const int grp = tid >> 4, gl = tid & 15;
     // columns of M = R^T (rows of R) placed in non-increasing order of their
     // norms (ties by index), which shortens the sweeps; the rotation
     // accumulator starts as that permutation
-    for (int j = grp; j < l; j += kJacThreads / 16) {
+    for (int j = grp; j < l; j += nth / 16) {
         double x = 0.0, y = 0.0, z = 0.0;
 #pragma unroll
-        for (int u = 0; u < kJacPer; ++u) {
+        for (int u = 0; u < PER; ++u) {
             const int e = gl + 16 * u;
             const double v = (e < l && e >= j) ? R[(int64_t)j * ldr + e] : 0.0;
             x += v * v;
@@ -129,107 +270,88 @@ __global__ __launch_bounds__(kJacThreads) void k_fact_jacobi(const double* __res
         group16_sum3(x, y, z);
         if (gl == 0) sig[j] = x;
     }
+    for (int i = tid; i < kJacSweeps; i += nth) rotated[i] = 0;
     __syncthreads();
-    if (tid < l) {
-        const double sj = sig[tid];
+    for (int j = tid; j < l; j += nth) {
+        const double sj = sig[j];
         int c = 0;
-        for (int i = 0; i < l; ++i) c += (sig[i] > sj || (sig[i] == sj && i < tid)) ? 1 : 0;
-        pos[tid] = c;
+        for (int i = 0; i < l; ++i) c += (sig[i] > sj || (sig[i] == sj && i < j)) ? 1 : 0;
+        pos[j] = c;
     }
     __syncthreads();
-    for (int idx = tid; idx < l * l; idx += kJacThreads) {
-        const int j = idx / l, i = idx - j * l;
-        Mc[pos[j]][i] = i >= j ? R[(int64_t)j * ldr + i] : 0.0;
-        Jc[pos[j]][i] = i == j ? 1.0 : 0.0;
+    for (int idx = tid; idx < 256 * PER * PER; idx += nth) {
+        const int j = idx / (16 * PER), i = idx - j * (16 * PER);
+        const int pj = j < l ? pos[j] : j;
+        Mc[pj][i] = (j < l && i < l && i >= j) ? R[(int64_t)j * ldr + i] : 0.0;
+        Jc[pj][i] = (j < l && i == j) ? 1.0 : 0.0;
     }
-    if (tid == 0) rotated = 0;
     __syncthreads();
-    const int L = l + (l & 1);
+    const int nb = nth / 32;   // blocks of four columns, two per wave
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), q = tid & 3, e0 = (tid & 63) >> 2;
     const double tol = (double)(l > 8 ? l : 8) * 0x1p-53;
     bool converged = false;
     for (int sweep = 0; sweep < kJacSweeps; ++sweep) {
-        int a = grp, b = L - 1;   // round 0's pair of this group (pair s = grp)
-        for (int t = 0; t + 1 < L; ++t) {
-            if (grp < L / 2) {
-                if (grp == 0) {
-                    a = t;
-                    b = L - 1;
-                } else {
-                    a = t + grp;
-                    a = a >= L - 1 ? a - (L - 1) : a;
-                    b = t - grp;
-                    b = b < 0 ? b + (L - 1) : b;
-                }
-                const int p = a < b ? a : b, q = a < b ? b : a;
-                if (q < l) {
-                    double mp[kJacPer], mq[kJacPer];
-                    double al = 0.0, be = 0.0, ga = 0.0;
-#pragma unroll
-                    for (int u = 0; u < kJacPer; ++u) {
-                        const int e = gl + 16 * u;
-                        mp[u] = e < l ? Mc[p][e] : 0.0;
-                        mq[u] = e < l ? Mc[q][e] : 0.0;
-                        al += mp[u] * mp[u];
-                        be += mq[u] * mq[u];
-                        ga += mp[u] * mq[u];
-                    }
-                    group16_sum3(al, be, ga);
-                    if (ga != 0.0 && __builtin_fabs(ga) > tol * __builtin_sqrt(al) * __builtin_sqrt(be)) {
-                        const double zeta = (be - al) / (2.0 * ga);
-                        const double az = __builtin_fabs(zeta);
-                        double tt = az > 1e150 ? 0.5 / az : 1.0 / (az + __builtin_sqrt(1.0 + zeta * zeta));
-                        tt = zeta < 0.0 ? -tt : tt;
-                        const double c = 1.0 / __builtin_sqrt(1.0 + tt * tt), sn = c * tt;
-#pragma unroll
-                        for (int u = 0; u < kJacPer; ++u) {
-                            const int e = gl + 16 * u;
-                            if (e < l) {
-                                Mc[p][e] = c * mp[u] - sn * mq[u];
-                                Mc[q][e] = sn * mp[u] + c * mq[u];
-                                const double jp = Jc[p][e], jq = Jc[q][e];
-                                Jc[p][e] = c * jp - sn * jq;
-                                Jc[q][e] = sn * jp + c * jq;
-                            }
-                        }
-                        if (gl == 0) rotated = 1;
-                    }
-                }
+        bool any = false;
+        for (int t = 0; t + 1 < nb; ++t) {
+            int x = t, y = nb - 1;
+            if (wave > 0) {
+                x = t + wave;
+                x = x >= nb - 1 ? x - (nb - 1) : x;
+                y = t - wave;
+                y = y < 0 ? y + (nb - 1) : y;
             }
+            const int pa = 4 * (x < y ? x : y), pb = 4 * (x < y ? y : x);
+            JacCol<PER> a, b;
+            a.load(&Mc[pa + q][e0], &Jc[pa + q][e0]);
+            b.load(&Mc[pb + q][e0], &Jc[pb + q][e0]);
+            if (t == 0) {
+                any |= jac_inside<PER, 1>(a, (q & 1) != 0, tol);
+                any |= jac_inside<PER, 1>(b, (q & 1) != 0, tol);
+                any |= jac_inside<PER, 2>(a, (q & 2) != 0, tol);
+                any |= jac_inside<PER, 2>(b, (q & 2) != 0, tol);
+                any |= jac_inside<PER, 3>(a, (q & 2) != 0, tol);
+                any |= jac_inside<PER, 3>(b, (q & 2) != 0, tol);
+            }
+            any |= jac_cross(a, b, tol);
+            b = b.template moved<1>();
+            any |= jac_cross(a, b, tol);
+            b = b.template moved<3>();
+            any |= jac_cross(a, b, tol);
+            b = b.template moved<1>();
+            any |= jac_cross(a, b, tol);
+            a.store(&Mc[pa + q][e0], &Jc[pa + q][e0]);
+            b.store(&Mc[pb + (q ^ 3)][e0], &Jc[pb + (q ^ 3)][e0]);
+            if (t + 2 == nb && any && (tid & 63) == 0) rotated[sweep] = 1;
             __syncthreads();
         }
-        const bool any = rotated != 0;
-        __syncthreads();   // every thread has read the flag
-        if (tid == 0) rotated = 0;
-        __syncthreads();   // the reset lands before the next sweep's rotations
-        if (!any) {
+        if (!rotated[sweep]) {
             converged = true;
             break;
         }
     }
     if (tid == 0 && !converged) *flag = 1;
     // singular values: one group of 16 lanes per column
-    for (int j = grp; j < l; j += kJacThreads / 16) {
+    for (int j = grp; j < l; j += nth / 16) {
         double x = 0.0, y = 0.0, z = 0.0;
 #pragma unroll
-        for (int u = 0; u < kJacPer; ++u) {
-            const int e = gl + 16 * u;
-            const double v = e < l ? Mc[j][e] : 0.0;
+        for (int u = 0; u < PER; ++u) {
+            const double v = Mc[j][gl + 16 * u];
             x += v * v;
         }
         group16_sum3(x, y, z);
         if (gl == 0) sig[j] = __builtin_sqrt(x);
     }
     __syncthreads();
-    if (tid < l) {
-        const double sj = sig[tid];
+    for (int j = tid; j < l; j += nth) {
+        const double sj = sig[j];
         int c = 0;
-        for (int i = 0; i < l; ++i) c += (sig[i] > sj || (sig[i] == sj && i < tid)) ? 1 : 0;
-        pos[tid] = c;
+        for (int i = 0; i < l; ++i) c += (sig[i] > sj || (sig[i] == sj && i < j)) ? 1 : 0;
+        pos[j] = c;
         sv[c] = sj;
         if (s_out && c < k) s_out[c] = sj;
     }
     __syncthreads();
-    for (int idx = tid; idx < l * ldw; idx += kJacThreads) {
+    for (int idx = tid; idx < l * ldw; idx += nth) {
         const int j = idx / ldw, e = idx - j * ldw;
         const double sj = sig[j];
         const int64_t o = (int64_t)pos[j] * ldw + e;
@@ -238,6 +360,17 @@ __global__ __launch_bounds__(kJacThreads) void k_fact_jacobi(const double* __res
         Zt[o] = z;
         if (Zts) Zts[o] = sj * z;
     }
+}
+
+template <int PER>
+static void launch_jacobi(const double* R, int l, int ldr, int k, double* sv, double* s_out, double* Wt, double* Zt,
+                          double* Zts, int* flag, hipStream_t st) {
+    if constexpr (PER < kFactMaxL / 16) {
+        if (l > 16 * PER)
+            return launch_jacobi<PER + 1>(R, l, ldr, k, sv, s_out, Wt, Zt, Zts, flag, st);
+    }
+    hipLaunchKernelGGL(k_fact_jacobi<PER>, dim3(1), dim3(64 * ((l + 7) / 8)), 0, st, R, l, ldr, k, sv, s_out, Wt, Zt,
+                       Zts, ldr, flag);
 }
 
 static unsigned fact_grid(int64_t items) {
@@ -312,8 +445,7 @@ hipError_t launch_rsvd(const double* A, int64_t m, int64_t n, int64_t lda, const
     LRC_STEP(launch_cholqr2(Bt, n, l, Q2, R, flags + 1, ws, st, "factor_cholqr2_f64", shifted));
     {
         KernelTimer tm("factor_jacobi_f64", st);
-        hipLaunchKernelGGL(k_fact_jacobi, dim3(1), dim3(kJacThreads), 0, st, R, l, rp, k, sv, s_out, Wt, Zt,
-                           Vts ? Zs : nullptr, rp, flags + 2);
+        launch_jacobi<1>(R, l, rp, k, sv, s_out, Wt, Zt, Vts ? Zs : nullptr, flags + 2, st);
     }
     if (U) LRC_STEP(launch_gemm_nt(Wt, rp, k, Q, rp, m, l, nullptr, U, ldu, k, ws, st, "factor_vectors_f64"));
     if (V) LRC_STEP(launch_gemm_nt(Zt, rp, k, Q2, rp, n, l, nullptr, V, ldv, k, ws, st, "factor_vectors_f64"));

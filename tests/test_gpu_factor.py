@@ -92,6 +92,30 @@ def test_rsvd_matches_oracle(lrc, m, n, l, k, q):
     _compare_rsvd(_gpu_rsvd(lrc, A, Om, k, q), ref, (m, n, l, k, q), so[k] if k < l else None)
 
 
+@pytest.mark.parametrize("l", [2, 7, 8, 9, 15, 16, 17, 32, 33, 48, 49, 64, 65, 80, 81, 95])
+def test_rsvd_every_jacobi_block_count(lrc, l):
+    """Sketch sizes at the edges of the Jacobi kernel's column blocks (two of
+    four columns per wave) and of its 16-entry column slices."""
+    m, n, k = l + 60, l + 41, max(1, l - 5)
+    A = _power_law(m, n, min(m, n), l, expo=1.0)
+    Om = synth.test_vectors(l, n, l)
+    print(f"rsvd l={l} k={k}", flush=True)
+    Uo, so, Vto = O.randomized_svd(A, Om, k + 1, 0)
+    _compare_rsvd(_gpu_rsvd(lrc, A, Om, k, 0), (Uo[:, :k], so[:k], Vto[:k]), l, so[k])
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -300, 2.0 ** 300])
+def test_rsvd_scaled_by_powers_of_two(lrc, scale):
+    """A power of two factor passes through exactly: the rotations scale their norms before they square them."""
+    A = _power_law(120, 90, 90, 5)
+    Om = synth.test_vectors(40, 90, 5)
+    U, s, V = _gpu_rsvd(lrc, A, Om, 30, 0)
+    Us, ss, Vs = _gpu_rsvd(lrc, A * scale, Om, 30, 0)
+    np.testing.assert_array_equal(ss, s * scale)
+    np.testing.assert_array_equal(Us, U)
+    np.testing.assert_array_equal(Vs, V)
+
+
 def test_rsvd_full_size_matrix(lrc):
     """8192 x 8192 with the matrix workload's law sigma_j = j^-1.5 (600
     terms), rank 65 from 75 test vectors: every singular value, sampled
