@@ -65,8 +65,9 @@ __global__ void k_fact_zero(int* p, int n) {
 template <int CTL>
 __device__ __forceinline__ double dpp_f64(double v) {
     const long long b = __builtin_bit_cast(long long, v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xFFFFFFFFll), CTL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTL, 0xF, 0xF, false);
+    // every lane receives a value, so there is no old one to keep
+    const int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xFFFFFFFFll), CTL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTL, 0xF, 0xF, false);
     return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
 }
 
@@ -194,13 +195,12 @@ __device__ __forceinline__ bool jac_cross(JacCol<PER>& a, JacCol<PER>& b, double
     double t, c, s;
     const double ga = stride4_sum(a.dot(b));
     const bool rot = jac_rotation(a.nn, b.nn, ga, tol, false, t, c, s);
-    if (__builtin_amdgcn_ballot_w64(rot) == 0) return false;
-    const JacCol<PER> a0 = a;
+    const JacCol<PER> a0 = a;   // applied without a branch: one would cost copies of all columns
     a.combine(c, -s, b);
     b.combine(c, s, a0);
     a.nn = __builtin_fma(-t, ga, a.nn);
     b.nn = __builtin_fma(t, ga, b.nn);
-    return true;
+    return __builtin_amdgcn_ballot_w64(rot) != 0;
 }
 
 // Pairs of the columns of one block, (q, q ^ X) for q = lane & 3: both lanes
@@ -211,10 +211,9 @@ __device__ __forceinline__ bool jac_inside(JacCol<PER>& a, bool second, double t
     const JacCol<PER> o = a.template moved<X>();
     const double ga = stride4_sum(a.dot(o));
     const bool rot = jac_rotation(a.nn, o.nn, ga, tol, second, t, c, s);
-    if (__builtin_amdgcn_ballot_w64(rot) == 0) return false;
     a.combine(c, -s, o);
     a.nn = __builtin_fma(-t, ga, a.nn);
-    return true;
+    return __builtin_amdgcn_ballot_w64(rot) != 0;
 }
 
 // One workgroup: SVD of M = R^T (R upper triangular, l x l inside pitch ldr)
@@ -240,7 +239,7 @@ __device__ __forceinline__ bool jac_inside(JacCol<PER>& a, bool second, double t
 // Bound by the issue of one compute unit and the chain dot - rotation -
 // update of a step, about 8 (4 ceil(l / 8) + 1) steps; a round per column
 // pair, with IEEE divisions and a trip through LDS each, took 1006 us at l = 74,
-// this takes 652.
+// this takes 601.
 constexpr int kJacPitch = 104;   // doubles: four neighbouring columns fall on distinct banks
 constexpr int kJacThreads = 64 * (kFactMaxL / 8);
 static_assert(kFactMaxL % 16 == 0 && kFactMaxL <= kJacPitch, "blocks of the largest sketch");
