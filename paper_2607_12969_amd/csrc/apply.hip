@@ -1442,7 +1442,143 @@ static void gram_plan(int64_t rows, int64_t cols, int* tiles, int* splits, int64
     *tiles = t;
 }
 
+// Grams of at most 96 columns (the orthonormalizations, small ranks): the F =
+// ceil(cols / 16) column fragments of four rows are both operands of the FP64
+// instruction as they come from memory, so each wave accumulates the whole
+// upper triangle of F (F + 1) / 2 fragments from its own rows, without LDS or
+// barriers, and P is read once.  A workgroup of eight waves takes a
+// contiguous chunk of rows, its waves every eighth step of four; their sums
+// meet in LDS and one partial per workgroup goes to k_gram_slim_finish.
+// Bound by the read: 114688 x 74 in 26 us (64 x 64 tiles through LDS: 69),
+// 32768 x 74 in 14 us (24).  At least 256 rows per workgroup, so that the
+// partials stay below the read; at most 256 workgroups, one per compute unit.
+constexpr int kSlimCols = 96, kSlimWaves = 8, kSlimGroup = 5;   // fragments summed over the waves at a time
+static int64_t slim_groups(int64_t rows) { return std::min<int64_t>((rows + 255) / 256, 256); }
+
+template <int F>
+__global__ __launch_bounds__(64 * kSlimWaves) void k_gram_slim(const double* __restrict__ P, int64_t ldp,
+                                                               int64_t rows, int cols, int64_t chunk,
+                                                               double4_t* __restrict__ part) {
+    constexpr int NF = F * (F + 1) / 2, U = F > 4 ? 2 : 4;      // fragments; steps loaded ahead
+    __shared__ double4_t red[kSlimWaves][kSlimGroup][64];
+    const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t beg = blockIdx.x * chunk, end = std::min(beg + chunk, rows);
+    int col[F];
+#pragma unroll
+    for (int f = 0; f < F; ++f) col[f] = std::min(16 * f + c, cols - 1);   // columns past the edge are not stored
+    double4_t acc[NF];
+#pragma unroll
+    for (int p = 0; p < NF; ++p) acc[p] = zero_accv<double4_t>();
+    double x[2][U][F];
+    auto fetch = [&](double(&d)[U][F], int64_t row0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t row = row0 + 4 * kSlimWaves * u + g;
+            const double* q = P + (row < end ? row : end - 1) * ldp;
+#pragma unroll
+            for (int f = 0; f < F; ++f) d[u][f] = q[col[f]];
+        }
+    };
+    auto product = [&](const double(&d)[U][F], int64_t row0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool in = row0 + 4 * kSlimWaves * u + g < end;
+            double y[F];
+#pragma unroll
+            for (int f = 0; f < F; ++f) y[f] = in ? d[u][f] : 0.0;
+#pragma unroll
+            for (int i = 0, p = 0; i < F; ++i)
+#pragma unroll
+                for (int j = i; j < F; ++j, ++p) acc[p] = mfma(y[i], y[j], acc[p]);
+        }
+    };
+    constexpr int64_t kStep = 4 * kSlimWaves * U;
+    const int64_t row0 = beg + 4 * wave;
+    fetch(x[0], row0);
+    for (int64_t r = row0; r < end; r += 2 * kStep) {
+        fetch(x[1], r + kStep);
+        product(x[0], r);
+        fetch(x[0], r + 2 * kStep);
+        product(x[1], r + kStep);
+    }
+#pragma unroll
+    for (int p0 = 0; p0 < NF; p0 += kSlimGroup) {
+        if (p0) __syncthreads();
+#pragma unroll
+        for (int p = 0; p < kSlimGroup; ++p)
+            if (p0 + p < NF) red[wave][p][lane] = acc[p0 + p];
+        __syncthreads();
+        const int p = tid >> 6;
+        if (p < kSlimGroup && p0 + p < NF) {
+            double4_t sum = red[0][p][lane];
+#pragma unroll
+            for (int w = 1; w < kSlimWaves; ++w) sum += red[w][p][lane];
+            part[((int64_t)blockIdx.x * NF + p0 + p) * 64 + lane] = sum;
+        }
+    }
+}
+
+// Sum of the workgroups' partials, in order within 16 runs of at most 16 and
+// over the runs, then G and its mirror image: one workgroup per fragment.
+template <int F>
+__global__ __launch_bounds__(1024) void k_gram_slim_finish(const double4_t* __restrict__ part, int groups, int cols,
+                                                           double* __restrict__ G, int64_t ldg) {
+    constexpr int NF = F * (F + 1) / 2;
+    __shared__ double4_t red[16][64];
+    const int lane = threadIdx.x & 63, run = threadIdx.x >> 6;
+    const double4_t* src = part + (int64_t)blockIdx.x * 64 + lane;
+    double4_t sum = zero_accv<double4_t>();
+    for (int b = 0; b < 16; b += 8) {
+        double4_t v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            v[u] = run * 16 + b + u < groups ? src[(int64_t)(run * 16 + b + u) * NF * 64] : zero_accv<double4_t>();
+#pragma unroll
+        for (int u = 0; u < 8; ++u) sum += v[u];
+    }
+    red[run][lane] = sum;
+    __syncthreads();
+    if (run != 0) return;
+#pragma unroll
+    for (int r = 1; r < 16; ++r) sum += red[r][lane];
+    int i = 0, j = blockIdx.x;
+    while (j >= F - i) {
+        j -= F - i;
+        ++i;
+    }
+    j += i;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int mm = 16 * i + acc_row<double>(lane >> 4, q), nn = 16 * j + (lane & 15);
+        if (nn < cols && mm <= nn) {
+            G[mm * ldg + nn] = sum[q];
+            G[nn * ldg + mm] = sum[q];
+        }
+    }
+}
+
+template <int F>
+static void gram_slim(const double* P, int64_t rows, int cols, double* G, double4_t* part, hipStream_t st) {
+    if constexpr (F < kSlimCols / 16) {
+        if (cols > 16 * F) return gram_slim<F + 1>(P, rows, cols, G, part, st);
+    }
+    const int64_t groups = slim_groups(rows), chunk = (rows + groups - 1) / groups;
+    {
+        KernelTimer t("cert_gram_f64", st);
+        hipLaunchKernelGGL(k_gram_slim<F>, dim3((unsigned)groups), dim3(64 * kSlimWaves), 0, st, P, (int64_t)cols,
+                           rows, cols, chunk, part);
+    }
+    KernelTimer t("cert_gram_finish_f64", st);
+    hipLaunchKernelGGL(k_gram_slim_finish<F>, dim3(F * (F + 1) / 2), dim3(1024), 0, st, part, (int)groups, cols, G,
+                       (int64_t)cols);
+}
+
 size_t gram_workspace_bytes(int64_t rows, int64_t cols) {
+    if (cols <= kSlimCols) {
+        const int64_t f = (cols + 15) / 16;
+        return (size_t)slim_groups(rows) * (f * (f + 1) / 2) * 64 * sizeof(double4_t);
+    }
     int t, sp;
     int64_t ch;
     gram_plan(rows, cols, &t, &sp, &ch);
@@ -1451,12 +1587,16 @@ size_t gram_workspace_bytes(int64_t rows, int64_t cols) {
 
 hipError_t launch_gram(const double* P, int64_t rows, int64_t cols, double* G, Workspace& ws,
                        hipStream_t stream) {
-    int t, sp;
-    int64_t ch;
-    gram_plan(rows, cols, &t, &sp, &ch);
     double* part = static_cast<double*>(ws.take(gram_workspace_bytes(rows, cols)));
     if (ws.overrun) return hipErrorOutOfMemory;
     if (!vec_ok<double>(P, cols)) return hipErrorInvalidValue;   // the factor builders keep 2r columns
+    if (cols <= kSlimCols) {
+        gram_slim<1>(P, rows, (int)cols, G, reinterpret_cast<double4_t*>(part), stream);
+        return hipGetLastError();
+    }
+    int t, sp;
+    int64_t ch;
+    gram_plan(rows, cols, &t, &sp, &ch);
     run_atb<double, GramC, ATB_GRAM>("cert_gram_f64", "cert_gram_finish_f64", stream, P, cols, P, cols, cols, cols,
                                      rows, ch, t, t, sp, part, (const double*)nullptr, (void*)G, cols, cols);
     return hipGetLastError();
@@ -1482,12 +1622,14 @@ hipError_t launch_err_dense(const double* A, const double* W, const double* Vw, 
 // Split-K partial tiles of C[m][n] = sum_{k in split} A[m][k] B[n][k] (both
 // sources K-contiguous, 16-byte aligned with even pitches), in the layout of
 // k_atb's partials (tile = n tile * tiles_m + m tile): k_atb_finish in
-// ATB_APPLY mode sums them in split order and stores C transposed.
+// ATB_APPLY mode sums them in split order and stores C transposed.  A sum
+// that is not split is stored at once.
 template <class C>
 __global__ __launch_bounds__(C::NT) void k_abt_part(const double* __restrict__ Asrc, int64_t lda, int64_t M,
                                                     const double* __restrict__ Bsrc, int64_t ldb, int64_t N,
                                                     int64_t K, int64_t chunk, int tiles_m, int tiles_n, int splits,
-                                                    double* __restrict__ part) {
+                                                    double* __restrict__ part, const double* __restrict__ svals,
+                                                    double* __restrict__ out, int64_t ldo, int64_t mout) {
     using AccV = typename C::AccV;
     constexpr int kAs = C::BM * C::LDK, kBs = C::BN * C::LDK;
     __shared__ alignas(16) double smem[2 * kAs + 2 * kBs];
@@ -1536,6 +1678,14 @@ __global__ __launch_bounds__(C::NT) void k_abt_part(const double* __restrict__ A
                                                    nfm, nfn);
             });
     });
+    if (splits == 1) {
+#pragma unroll
+        for (int fn = 0; fn < C::FN; ++fn)
+#pragma unroll
+            for (int fm = 0; fm < C::FM; ++fm)
+                atb_store<double, C, ATB_APPLY>(acc[fn][fm], tid, fn, fm, m0, n0, M, N, svals, out, ldo, mout);
+        return;
+    }
     constexpr int NF = C::FN * C::FM;
     AccV* mine = reinterpret_cast<AccV*>(part) + ((tile * splits + sp) * NF) * C::NT + tid;
 #pragma unroll
@@ -1544,34 +1694,51 @@ __global__ __launch_bounds__(C::NT) void k_abt_part(const double* __restrict__ A
         for (int fm = 0; fm < C::FM; ++fm) mine[(fn * C::FM + fm) * C::NT] = acc[fn][fm];
 }
 
-// Splits of a K range over `tiles` output tiles: about 1536 workgroups, at
+// Splits of a K range over `tiles` output tiles: about `target` workgroups, at
 // least 256 K values per split (chunk a multiple of the K step).
-static void split_plan(int64_t tiles, int64_t K, int* splits, int64_t* chunk) {
-    int64_t sp = (1536 + tiles - 1) / tiles;
+static void split_plan(int64_t tiles, int64_t K, int* splits, int64_t* chunk, int64_t target = 1536) {
+    int64_t sp = (target + tiles - 1) / tiles;
     int64_t mx = K / 256;
     if (mx < 1) mx = 1;
     if (sp > mx) sp = mx;
     if (sp < 1) sp = 1;
-    *chunk = round_up((K + sp - 1) / sp, GramC::BK);
+    *chunk = round_up((K + sp - 1) / sp, 2 * GramC::BK);
     *splits = (int)((K + *chunk - 1) / *chunk);
 }
 
 // At most 96 rows of W (the factorization's sketches and small factors) take
-// one 96-row tile, three fragments per wave (75 test vectors leave 21 of 96
-// rows idle instead of 53 of 128); wider W takes the 64 x 64 tiles.
-using NarrowC = Cfg<double, 96, 64, 16, 2, 2>;
+// one tile of as many fragments as W has, so that no wave has idle ones (the
+// wave's loop then has no guards); wider W takes the 64 x 64 tiles.  74 x
+// 512 over K = 114688 with the sum of the splits: 224 (96-row tiles, 1536
+// workgroups) -> 196 us.
+template <int F> using SlimC = Cfg<double, 16 * F, 64, 32, 1, 4>;
+// Two of their workgroups share a compute unit: one wave of 512.
+template <class C> static constexpr int64_t nt_target() { return C::WM == 1 ? 512 : 1536; }
 
 template <class C>
 static size_t gemm_nt_bytes(int64_t nw, int64_t rows, int64_t K) {
     const int64_t tiles = tiles_of(nw, C::BM) * tiles_of(rows, C::BN);
     int sp;
     int64_t ch;
-    split_plan(tiles, K, &sp, &ch);
-    return (size_t)tiles * sp * C::BM * C::BN * sizeof(double);
+    split_plan(tiles, K, &sp, &ch, nt_target<C>());
+    return sp > 1 ? (size_t)tiles * sp * C::BM * C::BN * sizeof(double) : 0;
+}
+
+template <class Fn>
+static auto by_fragments(int64_t nw, Fn&& fn) {
+    switch ((nw + 15) / 16) {
+    case 1: return fn(SlimC<1>{});
+    case 2: return fn(SlimC<2>{});
+    case 3: return fn(SlimC<3>{});
+    case 4: return fn(SlimC<4>{});
+    case 5: return fn(SlimC<5>{});
+    case 6: return fn(SlimC<6>{});
+    default: return fn(GramC{});
+    }
 }
 
 size_t gemm_nt_workspace_bytes(int64_t nw, int64_t rows, int64_t K) {
-    return nw <= NarrowC::BM ? gemm_nt_bytes<NarrowC>(nw, rows, K) : gemm_nt_bytes<GramC>(nw, rows, K);
+    return by_fragments(nw, [&](auto c) { return gemm_nt_bytes<decltype(c)>(nw, rows, K); });
 }
 
 template <class C>
@@ -1583,13 +1750,17 @@ static hipError_t gemm_nt_typed(const double* W, int64_t ldw, int64_t nw, const 
         return hipErrorInvalidValue;
     int sp;
     int64_t ch;
-    split_plan((int64_t)tm * tn, K, &sp, &ch);
-    double* part = static_cast<double*>(ws.take(gemm_nt_bytes<C>(nw, rows, K)));
-    if (ws.overrun) return hipErrorOutOfMemory;
+    split_plan((int64_t)tm * tn, K, &sp, &ch, nt_target<C>());
+    double* part = nullptr;
+    if (sp > 1) {
+        part = static_cast<double*>(ws.take(gemm_nt_bytes<C>(nw, rows, K)));
+        if (ws.overrun) return hipErrorOutOfMemory;
+    }
     KernelTimer t(label, stream);
     hipLaunchKernelGGL(k_abt_part<C>, dim3(xcd_grid((int64_t)tm * tn * sp)), dim3(C::NT), 0, stream, W, ldw, nw, A,
-                       lda, rows, K, ch, tm, tn, sp, part);
-    hipLaunchKernelGGL((k_atb_finish<double, C, ATB_APPLY>),
+                       lda, rows, K, ch, tm, tn, sp, part, svals, out, ldo, mout);
+    if (sp > 1)
+        hipLaunchKernelGGL((k_atb_finish<double, C, ATB_APPLY>),
                        dim3((unsigned)((int64_t)tm * tn * C::FN * C::FM * (C::NT / 64))), dim3(64 * kFinishRuns), 0,
                        stream, reinterpret_cast<const typename C::AccV*>(part), nw, rows, tm, sp, svals, (void*)out,
                        ldo, mout);
@@ -1599,9 +1770,104 @@ static hipError_t gemm_nt_typed(const double* W, int64_t ldw, int64_t nw, const 
 hipError_t launch_gemm_nt(const double* W, int64_t ldw, int64_t nw, const double* A, int64_t lda, int64_t rows,
                           int64_t K, const double* svals, double* out, int64_t ldo, int64_t mout, Workspace& ws,
                           hipStream_t stream, const char* label) {
-    if (nw <= NarrowC::BM)
-        return gemm_nt_typed<NarrowC>(W, ldw, nw, A, lda, rows, K, svals, out, ldo, mout, ws, stream, label);
-    return gemm_nt_typed<GramC>(W, ldw, nw, A, lda, rows, K, svals, out, ldo, mout, ws, stream, label);
+    return by_fragments(nw, [&](auto c) {
+        return gemm_nt_typed<decltype(c)>(W, ldw, nw, A, lda, rows, K, svals, out, ldo, mout, ws, stream, label);
+    });
+}
+
+// out[c][j] = sum_k A[k][c] Q[k][j] for at most 96 columns of Q (F fragments of
+// 16) and at least 32768 of A: both operands have the product's K as their
+// row index, so the fragments are read straight from memory.  A wave takes
+// 64 columns of A, lane (g, c) the pairs n0 + 2 c and n0 + 32 + 2 c of row k
+// + g, and all of Q, which the caches hold; nothing is shared and nothing
+// waits.  114688 columns, K = 512, 74 of Q: 209 us (64 x 64 tiles, half of the
+// second one idle: 267; matrix cores alone: 120).  With fewer columns there
+// are too few waves for the chip (32768: 512) and the split tiles below take
+// over.
+constexpr int64_t kSlimTnCols = 32768;
+template <int F>
+__global__ __launch_bounds__(256, 2) void k_tn_slim(const double* __restrict__ Q, int64_t ldq, int nq,
+                                                    const double* __restrict__ A, int64_t lda, int64_t cols, int64_t K,
+                                                    double* __restrict__ out, int64_t ldo, int mout) {
+    const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t n0 = ((int64_t)blockIdx.x * 4 + wave) * 64;
+    if (n0 >= cols) return;
+    int64_t ca[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        ca[h] = n0 + 32 * h + 2 * c;
+        ca[h] = ca[h] < cols ? ca[h] : 0;   // even, so the pair lies inside the pitch
+    }
+    int cq[F];
+#pragma unroll
+    for (int f = 0; f < F; ++f) cq[f] = std::min(16 * f + c, nq - 1);
+    double4_t acc[4][F];
+#pragma unroll
+    for (int h = 0; h < 4; ++h)
+#pragma unroll
+        for (int f = 0; f < F; ++f) acc[h][f] = zero_accv<double4_t>();
+    constexpr int DA = F > 5 ? 2 : 4;   // steps of A under way (memory), one of Q (cache)
+    double2 xa[DA][2];
+    double xq[2][F];
+    auto fetch_a = [&](double2(&d)[2], int64_t k0) {
+        const double* p = A + (k0 + g < K ? k0 + g : K - 1) * lda;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) d[h] = *reinterpret_cast<const double2*>(p + ca[h]);
+    };
+    auto fetch_q = [&](double(&d)[F], int64_t k0) {
+        const double* p = Q + (k0 + g < K ? k0 + g : K - 1) * ldq;
+#pragma unroll
+        for (int f = 0; f < F; ++f) d[f] = p[cq[f]];
+    };
+    auto product = [&](const double2(&x)[2], const double(&y)[F], int64_t k0) {
+        const bool in = k0 + g < K;
+        double a[4], q[F];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            a[2 * h] = in ? x[h].x : 0.0;
+            a[2 * h + 1] = in ? x[h].y : 0.0;
+        }
+#pragma unroll
+        for (int f = 0; f < F; ++f) q[f] = in ? y[f] : 0.0;
+#pragma unroll
+        for (int f = 0; f < F; ++f)
+#pragma unroll
+            for (int h = 0; h < 4; ++h) acc[h][f] = mfma(a[h], q[f], acc[h][f]);
+    };
+#pragma unroll
+    for (int u = 0; u < DA; ++u) fetch_a(xa[u], 4 * u);
+    fetch_q(xq[0], 0);
+    for (int64_t k = 0; k < K; k += 4 * DA) {
+#pragma unroll
+        for (int u = 0; u < DA; ++u) {
+            fetch_q(xq[(u + 1) & 1], k + 4 * u + 4);
+            product(xa[u], xq[u & 1], k + 4 * u);
+            fetch_a(xa[u], k + 4 * (u + DA));
+        }
+    }
+#pragma unroll
+    for (int h = 0; h < 4; ++h)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int64_t n = n0 + 32 * (h >> 1) + 2 * acc_row<double>(g, v) + (h & 1);
+            if (n >= cols) continue;
+#pragma unroll
+            for (int f = 0; f < F; ++f) {
+                const int j = 16 * f + c;
+                if (j < mout) out[n * ldo + j] = j < nq ? acc[h][f][v] : 0.0;
+            }
+        }
+}
+
+template <int F>
+static void tn_slim(const double* Q, int64_t ldq, int nq, const double* A, int64_t lda, int64_t cols, int64_t K,
+                    double* out, int64_t ldo, int mout, hipStream_t st) {
+    if constexpr (F < 6) {
+        if (mout > 16 * F) return tn_slim<F + 1>(Q, ldq, nq, A, lda, cols, K, out, ldo, mout, st);
+    }
+    hipLaunchKernelGGL(k_tn_slim<F>, dim3((unsigned)((cols + 255) / 256)), dim3(256), 0, st, Q, ldq, nq, A, lda, cols,
+                       K, out, ldo, mout);
 }
 
 size_t gemm_tn_workspace_bytes(int64_t nq, int64_t cols, int64_t K) {
@@ -1618,6 +1884,11 @@ hipError_t launch_gemm_tn(const double* Q, int64_t ldq, int64_t nq, const double
     const int tm = (int)tiles_of(nq, GramC::BM), tn = (int)tiles_of(cols, GramC::BN);
     if (!vec_ok<double>(Q, ldq) || !vec_ok<double>(A, lda) || mout < nq || mout > (int64_t)tm * GramC::BM)
         return hipErrorInvalidValue;
+    if (mout <= 96 && cols >= kSlimTnCols) {
+        KernelTimer t(label, stream);
+        tn_slim<1>(Q, ldq, (int)nq, A, lda, cols, K, out, ldo, (int)mout, stream);
+        return hipGetLastError();
+    }
     int sp;
     int64_t ch;
     split_plan((int64_t)tm * tn, K, &sp, &ch);

@@ -104,6 +104,19 @@ def test_rsvd_every_jacobi_block_count(lrc, l):
     _compare_rsvd(_gpu_rsvd(lrc, A, Om, k, 0), (Uo[:, :k], so[:k], Vto[:k]), l, so[k])
 
 
+@pytest.mark.parametrize("m,n,l", [(37, 32768, 5), (101, 32770, 22), (80, 32831, 47), (131, 33001, 96), (90, 32767, 65)])
+def test_rsvd_wide_matrix(lrc, m, n, l):
+    """A^T Q straight from memory (32768 columns and more): ragged tiles of 64
+    columns, odd widths, rows past a multiple of the K step; one width below it."""
+    l = min(l, m)
+    A = _power_law(m, n, m, l, expo=1.0)
+    Om = synth.test_vectors(l, n, l)
+    print(f"rsvd m={m} n={n} l={l}", flush=True)
+    k = l - 2
+    Uo, so, Vto = O.randomized_svd(A, Om, k + 1, 0)
+    _compare_rsvd(_gpu_rsvd(lrc, A, Om, k, 0), (Uo[:, :k], so[:k], Vto[:k]), (m, n, l), so[k])
+
+
 @pytest.mark.parametrize("scale", [2.0 ** -300, 2.0 ** 300])
 def test_rsvd_scaled_by_powers_of_two(lrc, scale):
     """A power of two factor passes through exactly: the rotations scale their norms before they square them."""
