@@ -513,8 +513,8 @@ __device__ __forceinline__ void atb_store(const typename C::AccV& a, int tid, in
 //              factor 1 when s is null),
 //              written for m < Mout (zero padding rows included).
 //   ATB_GRAM : out is G[m][ldo] in double (T = double).
-// MIS: A has a misaligned base or pitch and is read in place; B is aligned.
-template <typename T, class C, int MODE, bool MIS = false>
+// MIS, MISB: A, B has a misaligned base or pitch and is read in place.
+template <typename T, class C, int MODE, bool MIS = false, bool MISB = false>
 __global__ __launch_bounds__(C::NT) void k_atb(
     const T* __restrict__ Asrc, int64_t lda, const T* __restrict__ Bsrc, int64_t ldb,
     int64_t M, int64_t N, int64_t K, int64_t chunk, int tiles_m, int tiles_n, int splits,
@@ -545,9 +545,9 @@ __global__ __launch_bounds__(C::NT) void k_atb(
         for (int fm = 0; fm < C::FM; ++fm) acc[fn][fm] = zero_accv<AccV>();
 
     using TA = RowsTile<C, C::BM, T, MIS>;
-    using TB = RowsTile<C, C::BN, T>;   // X (or the certificate's factor): aligned rows
+    using TB = RowsTile<C, C::BN, T, MISB>;   // X (or the certificate's factor)
     const typename TA::Geo ga = TA::geo(Asrc, lda, m0, M, tid, Asrc + (K - 1) * lda + (M - 1));
-    const typename TB::Geo gb = TB::geo(Bsrc, ldb, n0, N, tid);
+    const typename TB::Geo gb = TB::geo(Bsrc, ldb, n0, N, tid, Bsrc + (K - 1) * ldb + (N - 1));
     TA ta[2];
     TB tb[2];
     const int nsteps = (int)((kend - kbeg + C::BK - 1) / C::BK);
@@ -825,14 +825,14 @@ static bool vec_ok(const void* p, int64_t ld) {
 }
 
 // k_atb over all (tile, split) workgroups, then k_atb_finish when the sum is split.
-template <typename T, class C, int MODE, bool MIS = false>
+template <typename T, class C, int MODE, bool MIS = false, bool MISB = false>
 static void run_atb(const char* label, const char* finish_label, hipStream_t st, const T* A, int64_t lda,
                     const T* B, int64_t ldb, int64_t M, int64_t N, int64_t K, int64_t chunk, int tiles_m, int tiles_n,
                     int splits, typename C::Acc* part, const T* svals, void* out, int64_t ldo, int64_t Mout) {
     {
         KernelTimer t(label, st);
         const dim3 grid(xcd_grid((int64_t)tiles_m * tiles_n * splits));
-        hipLaunchKernelGGL((k_atb<T, C, MODE, MIS>), grid, dim3(C::NT), 0, st, A, lda, B, ldb, M, N, K, chunk,
+        hipLaunchKernelGGL((k_atb<T, C, MODE, MIS, MISB>), grid, dim3(C::NT), 0, st, A, lda, B, ldb, M, N, K, chunk,
                            tiles_m, tiles_n, splits, part, svals, out, ldo, Mout);
     }
     if (splits > 1) {
@@ -1228,7 +1228,16 @@ ApplyPlan plan_apply(int64_t m, int64_t n, int64_t k, int64_t b, int prec, int p
         // extra launch costs more than the shifts; otherwise the factor is
         // copied to a padded pitch once per call (measured at 8192 x 8192,
         // batch 4096: in place, phases 1 and 2 each lose 15-25 %, more than
-        // the copy costs).  A misaligned X is always copied.
+        // the copy costs).  A misaligned X is read by every rank tile: in place
+        // by few of them or when those reads add up to little, since the copy
+        // then costs a launch and two passes over X (8192 x 8192 FP64, k = 64:
+        // batch 4095 315 -> 221 us, batch 129 36.7 -> 33.2 us; 2003 x 1733
+        // FP16, k = 41, batch 2047 30.2 -> 24.7 us; but 1024 x 8000 FP64, k =
+        // 129, batch 129, three tiles, 41.3 against 43.0 us in place, and k =
+        // 400, batch 2047 319 against 345 us).  Where U or V is copied anyway
+        // the launch is not saved and only a large X gains (30000 x 2000 FP64,
+        // k = 41: batch 513 95.3 against 96.2 us in place, batch 2047 243
+        // against 234 us).
         const TileDims d1 = cfg_dims(prec, p.big1), d2 = cfg_dims(prec, p.big2);
         const size_t e = elem_bytes(prec);
         const bool u_bad = needs_stage(U, k, prec), v_bad = needs_stage(V, k, prec);
@@ -1237,13 +1246,21 @@ ApplyPlan plan_apply(int64_t m, int64_t n, int64_t k, int64_t b, int prec, int p
         p.mis2 = (u_bad && (reads2 <= 1 || (size_t)m * k * e * reads2 <= kInPlaceBytes)) ? 1 : 0;
         p.stage_u = (u_bad && !p.mis2) ? 1 : 0;
         p.stage_v = (v_bad && !p.mis1) ? 1 : 0;
-        p.stage_x = needs_stage(X, b, prec) ? 1 : 0;
+        const bool x_bad = needs_stage(X, b, prec);
+        const size_t xbytes = (size_t)n * b * e;
+        const bool alone = !p.stage_u && !p.stage_v;
+        p.misx = x_bad && ((alone && (p.tiles_m <= (e < 8 ? 4 : 2) || xbytes * p.tiles_m <= kInPlaceBytes)) ||
+                           (p.tiles_m <= 1 && xbytes >= kInPlaceBytes) ||
+                           (p.tiles_m <= 4 && xbytes >= 4 * kInPlaceBytes));
+        p.stage_x = (x_bad && !p.misx) ? 1 : 0;
         p.ldx = round_up(b, 8);
         p.stage_bytes = (p.stage_u ? round_up((size_t)m * p.Kp * e, 256) : 0) +
                         (p.stage_v ? round_up((size_t)n * p.Kp * e, 256) : 0) +
                         (p.stage_x ? round_up((size_t)n * p.ldx * e, 256) : 0);
     }
-    p.scratch_bytes = apply_workspace_bytes(p);
+    // the allocation-free entry takes what it took when X was always copied
+    p.scratch_bytes = apply_workspace_bytes(p) +
+                      (p.misx ? round_up((size_t)n * p.ldx * elem_bytes(prec), 256) : 0);
     if (path == 2 && !forced_tile()) {
         if (small_takes(m, n, k, b)) {
             p.small = 1;
@@ -1368,14 +1385,17 @@ static hipError_t apply_typed(const ApplyPlan& p, const T* U, const T* s, const 
     using Small = typename SmallCfg<T>::C;
     const char *l1 = p1_mfma_label<T>(), *lf = p1_finish_label<T>();
 #define LRC_P1(CFG, MISV)                                                                                        \
-    run_atb<T, CFG, ATB_APPLY, MISV>(l1, lf, stream, Vg, ldv, Xg, ldx, k, b, n, p.chunk, p.tiles_m, p.tiles_n,     \
+    if (p.misx) LRC_P1X(CFG, MISV, true); else LRC_P1X(CFG, MISV, false)
+#define LRC_P1X(CFG, MISV, MISX)                                                                                 \
+    run_atb<T, CFG, ATB_APPLY, MISV, MISX>(l1, lf, stream, Vg, ldv, Xg, ldx, k, b, n, p.chunk, p.tiles_m, p.tiles_n,     \
                                      p.splits, part, s, (void*)Tt, ldt, ldt)
     if (p.big1) {
-        if (p.mis1) LRC_P1(Big, true); else LRC_P1(Big, false);
+        if (p.mis1) { LRC_P1(Big, true); } else { LRC_P1(Big, false); }
     } else {
-        if (p.mis1) LRC_P1(Small, true); else LRC_P1(Small, false);
+        if (p.mis1) { LRC_P1(Small, true); } else { LRC_P1(Small, false); }
     }
 #undef LRC_P1
+#undef LRC_P1X
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     KernelTimer t2(p2_mfma_label<T>(), stream);

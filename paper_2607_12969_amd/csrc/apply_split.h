@@ -457,7 +457,7 @@ static bool x3_takes(int64_t m, int64_t n, int64_t k, int64_t b, int prec, const
 static void x3_plan(ApplyPlan& p, int64_t m, int64_t n, int64_t k, int64_t b) {
     const int64_t frags = (k + 15) / 16;
     p.x3 = 1;
-    p.mis1 = p.mis2 = p.stage_u = p.stage_v = p.stage_x = 0;
+    p.mis1 = p.mis2 = p.misx = p.stage_u = p.stage_v = p.stage_x = 0;
     p.tiles_m = (int)((frags + 16) / 17);
     p.nf = (int)((frags + p.tiles_m - 1) / p.tiles_m);
     p.tiles_n = (int)((b + 127) / 128);

@@ -54,10 +54,10 @@ struct ApplyPlan {
     int big1, big2;      // 128 x 128 tiles (else 64 x 64) for phase 1 / phase 2
     // MFMA path, operands whose base or pitch rules out aligned 16-byte moves
     // (odd ranks such as the compensated k + 1, odd batches): V (phase 1,
-    // mis1) and U (phase 2, mis2) are read in place when they are small or
-    // read by a single tile of the other dimension; otherwise U, V (pitch Kp)
-    // and X (pitch ldx) are copied to a padded pitch first
-    int mis1, mis2;
+    // mis1), U (phase 2, mis2) and X (phase 1, misx) are read in place when
+    // they are small or read by few tiles of the other dimension; otherwise
+    // U, V (pitch Kp) and X (pitch ldx) are copied to a padded pitch first
+    int mis1, mis2, misx;
     int stage_u, stage_v, stage_x;
     int64_t ldx;
     // FP32 by split products on the bfloat16 matrix cores (large batches): rank

@@ -227,6 +227,29 @@ def test_large_rank_small_batch(lrc):
 
 
 @pytest.mark.parametrize("prec", PRECS)
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("m,n,k,b", [
+    (300, 2111, 48, 77), (300, 2100, 33, 131),     # one rank tile, even and odd rank, several splits
+    (520, 900, 130, 259), (256, 1000, 200, 257),   # 64- and 128-row tiles, read several times
+    (700, 1501, 257, 35), (300, 33, 17, 2051),     # five rank tiles, one split
+    (9001, 1030, 65, 1025),                        # U copied, X by size
+])
+def test_odd_batches(lrc, m, n, k, b, shift, prec):
+    """X at a pitch (and, shifted, a base) that rules out 16-byte moves: in place or copied."""
+    import torch
+    d = synth.random_factors(m, n, k, b, tag=m + n + k + b)
+    hs = [stored_pair(d[f], prec) for f in ("U", "s", "V", "X")]
+    dev = [to_dev(h) for h, _ in hs]
+    buf = torch.empty(n * b + shift, dtype=dev[3].dtype, device="cuda")
+    x = buf[shift:].view(n, b)
+    x.copy_(dev[3])
+    print(f"apply odd batch prec={prec} m={m} n={n} k={k} b={b} shift={shift}", flush=True)
+    Y = lrc.matrix_apply(dev[0], dev[1], dev[2], x)
+    torch.cuda.synchronize()
+    _assert_parity(Y.cpu().numpy().astype(np.float64), *[o for _, o in hs], prec)
+
+
+@pytest.mark.parametrize("prec", PRECS)
 @pytest.mark.parametrize("m,n,k,b", [
     (65, 9, 9, 17),         # one row and column past a tile, waves without rows
     (512, 256, 20, 64),     # whole batches of rows
