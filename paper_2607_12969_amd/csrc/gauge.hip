@@ -379,9 +379,10 @@ __global__ void k_gauge_zero(int* p, int n) {
     for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
 }
 
-// Two row tiles per wave share each fragment of R once that leaves four
-// waves on every SIMD's queue; the grid is bounded so that a workgroup's
-// set-up (R to LDS, diagonal blocks inverted) is spread over several tiles.
+// Two row tiles per wave share each fragment of R where that still leaves a
+// wave for every SIMD (1024 waves of 32 rows); the grid is bounded so that a
+// workgroup's set-up (R to LDS, diagonal blocks inverted, most of the 13 us
+// that 512 rows take) is spread over several tiles.
 template <int NB>
 static void launch_trsm_nb(const double* A, int64_t rows, int r, int lda, const double* R, int ldr, double* C,
                            int ldc, hipStream_t st) {
