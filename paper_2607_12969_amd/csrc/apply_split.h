@@ -19,7 +19,6 @@
 typedef __bf16 bf2_t __attribute__((ext_vector_type(2)));
 typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
 typedef float f2_t __attribute__((ext_vector_type(2)));
-typedef unsigned short us2_t __attribute__((ext_vector_type(2)));
 typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
 
 constexpr int kX3BK = 32;           // K step: one bfloat16 MFMA
@@ -44,18 +43,19 @@ __device__ __forceinline__ float x3_poison(float x) {
 }
 
 // Range of the values split on the way: largest magnitude and smallest
-// nonzero one (as 2 bits - 1 of the first part, the sign shifted out; zero
-// wraps to the largest key).
+// nonzero one (as the value's bits, the sign shifted out, minus 1; zero
+// wraps to the largest key).  The value itself decides, not its first part,
+// which is zero for subnormals below 2^-134.
 struct X3Range {
     float mx = 0.0f;
-    us2_t mn = {0xFFFF, 0xFFFF};
-    __device__ __forceinline__ void add(float a, float b, unsigned p1) {
+    unsigned mn = ~0u;
+    __device__ __forceinline__ void add(float a, float b) {
         mx = __builtin_fmaxf(__builtin_fmaxf(mx, __builtin_fabsf(a)), __builtin_fabsf(b));
-        mn = __builtin_elementwise_min(mn, __builtin_bit_cast(us2_t, p1) * (unsigned short)2 + (unsigned short)0xFFFF);
+        mn = std::min(mn, std::min(__builtin_bit_cast(unsigned, a) * 2u - 1u, __builtin_bit_cast(unsigned, b) * 2u - 1u));
     }
     __device__ __forceinline__ bool bad() const {
-        constexpr unsigned short kKey = 2 * ((127 - 100) << 7) - 1;   // of 2^-100
-        return !(mx < kX3Max) || mn[0] < kKey || mn[1] < kKey;
+        constexpr unsigned kKey = 2u * ((127u - 100u) << 23) - 1u;   // of 2^-100
+        return !(mx < kX3Max) || mn < kKey;
     }
 };
 
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(256, 2) void k_p1_x3(const unsigned short* __restri
             for (int q = 0; q < 4; ++q) {
                 unsigned p[3];
                 x3_split2(xr[h][2 * q], xr[h][2 * q + 1], p);
-                range.add(xr[h][2 * q], xr[h][2 * q + 1], p[0]);
+                range.add(xr[h][2 * q], xr[h][2 * q + 1]);
 #pragma unroll
                 for (int t = 0; t < 3; ++t) pk[t][q] = p[t];
             }

@@ -345,3 +345,21 @@ def test_fp32_split_special_values(lrc, what):
     for cols in (slice(0, 3000), slice(3000, b)):
         ok = np.isfinite(ref[:, cols])
         assert rel_fro(np.where(ok, Y[:, cols], 0), np.where(ok, ref[:, cols], 0)) <= TOL["fp32"]
+
+
+def test_fp32_split_subnormal_columns(lrc):
+    """Columns of X below 2^-134, whose bfloat16 part is zero, against V and U
+    large enough to carry them to ordinary outputs, beside normal columns."""
+    m, n, k, b = 1030, 1500, 70, 8200
+    d = synth.random_factors(m, n, k, b, tag=10)
+    U, s, V, X = (np.array(d[q], dtype=np.float32) for q in ("U", "s", "V", "X"))
+    U *= np.float32(2.0 ** 60)
+    V *= np.float32(2.0 ** 40)
+    tiny = slice(4000, 4300)
+    X[:, tiny] = np.float32(2.0 ** -140) * np.sign(X[:, tiny])
+    X[:, 4100] = 0
+    X[11, 4100] = np.float32(2.0 ** -149)
+    Y = lrc.matrix_apply(*[to_dev(a) for a in (U, s, V, X)]).cpu().numpy()
+    ref = U.astype(np.float64) @ (s.astype(np.float64)[:, None] * (V.astype(np.float64).T @ X.astype(np.float64)))
+    for cols in (slice(0, 4000), tiny, slice(4100, 4101), slice(4300, b)):
+        assert rel_fro(Y[:, cols], ref[:, cols]) <= TOL["fp32"]
