@@ -24,6 +24,7 @@
 #include <cstdlib>
 #include <type_traits>
 
+#include "../../include/lrc.h"
 #include "lrc_device.h"
 #include "lrc_internal.h"
 
@@ -1266,7 +1267,8 @@ ApplyPlan plan_apply(int64_t m, int64_t n, int64_t k, int64_t b, int prec, int p
             p.small = 1;
             p.part_bytes = p.mid_bytes = p.stage_bytes = 0;
         } else if (x3_takes(m, n, k, b, prec, U, V, X)) {
-            x3_plan(p, m, n, k, b);
+            ApplyPlan q = p;
+            if (x3_plan(q, m, n, k, b)) p = q;
         }
     }
     return p;

@@ -425,9 +425,9 @@ __global__ __launch_bounds__(256, 2) void k_p2_x3(const unsigned short* __restri
 }
 
 // ---- host ------------------------------------------------------------------------
-// Bytes that the rows of V, a column panel and a row panel of U may each be
-// cut to (x3_panels), chosen so that the cuts fit the allocation-free entry's
-// scratch; larger factors keep the FP32 instruction.
+// About the bytes of V's planes per split and of a column's partial sums; factors
+// too large for both keep the FP32 instruction.  Panels of such sizes fit the
+// allocation-free entry's scratch (x3_plan makes sure).
 constexpr int64_t kX3VBytes = (int64_t)16 << 20, kX3ColBytes = (int64_t)128 << 10;
 
 // Sizes that gain from the split (old and new times on the grid 512 <= m, n <=
@@ -453,8 +453,10 @@ static bool x3_takes(int64_t m, int64_t n, int64_t k, int64_t b, int prec, const
 // Fragments per rank tile: at most 17, so that ranks 16 j + 1 (a compensated
 // rank past a round one) up to 257 stay one tile.  Row chunks for about two
 // workgroups per compute unit (256 instead of 512: 136 against 101 us at
-// 8192 x 8192, k = 257, b = 4096), at least 128 rows each.
-static void x3_plan(ApplyPlan& p, int64_t m, int64_t n, int64_t k, int64_t b) {
+// 8192 x 8192, k = 257, b = 4096), at least 128 rows each.  False (p unusable):
+// a call that the allocation-free entry takes (p.scratch_bytes) would not fit
+// its scratch; both entries then keep the FP32 instruction, with equal bits.
+static bool x3_plan(ApplyPlan& p, int64_t m, int64_t n, int64_t k, int64_t b) {
     const int64_t frags = (k + 15) / 16;
     p.x3 = 1;
     p.mis1 = p.mis2 = p.misx = p.stage_u = p.stage_v = p.stage_x = 0;
@@ -470,13 +472,16 @@ static void x3_plan(ApplyPlan& p, int64_t m, int64_t n, int64_t k, int64_t b) {
     if (splits < 1) splits = 1;
     p.chunk = round_up((n + splits - 1) / splits, kX3BK);
     p.splits = (int)((n + p.chunk - 1) / p.chunk);
-    x3_panels(p, m, b, (size_t)1 << 30);
+    const size_t noalloc = (size_t)LRC_NOALLOC_SCRATCH_BYTES;
+    return (p.scratch_bytes > noalloc || x3_panels(p, m, b, noalloc)) && x3_panels(p, m, b, (size_t)1 << 30);
 }
 
 // Panels within `limit` bytes of scratch: splits whose planes of V^T are held
-// at a time, columns of the batch and rows of U.  Every output value is the
-// same whatever the panels.
-void x3_panels(ApplyPlan& p, int64_t m, int64_t b, size_t limit) {
+// at a time, columns of the batch and rows of U.  V takes up to a quarter (one
+// split at least), columns and rows share two to one what it leaves.  Every
+// output value is the same whatever the panels.  False: not even panels of 128
+// columns and rows fit, the plan is not usable.
+bool x3_panels(ApplyPlan& p, int64_t m, int64_t b, size_t limit) {
     const int64_t vsplit = 6 * p.kpad * p.chunk, col = (int64_t)p.splits * p.kpad * 4 + p.Kp * 4 + 6 * p.ldk;
     const int64_t row = 6 * p.ldk, room = (int64_t)limit - 4096;
     p.vgroup = p.splits;
@@ -484,13 +489,16 @@ void x3_panels(ApplyPlan& p, int64_t m, int64_t b, size_t limit) {
     p.mpanel = m;
     if (vsplit * p.vgroup + col * b + row * m > room) {
         p.vgroup = std::max<int64_t>(1, std::min<int64_t>(p.splits, room / 4 / vsplit));
-        p.mpanel = std::min(m, std::max<int64_t>(128, room / 4 / row / 128 * 128));
-        p.bpanel = std::min(b, std::max<int64_t>(128, room / 2 / col / 128 * 128));
+        const int64_t left = room - p.vgroup * vsplit;
+        p.bpanel = std::min(b, left / 3 * 2 / col / 128 * 128);
+        p.mpanel = std::min(m, (left - p.bpanel * col) / row / 128 * 128);
+        if (p.bpanel < std::min<int64_t>(b, 128) || p.mpanel < std::min<int64_t>(m, 128)) return false;
     }
     p.part_bytes = (size_t)p.splits * p.bpanel * p.kpad * 4;
     p.mid_bytes = (size_t)p.bpanel * p.Kp * 4;
     p.stage_bytes = round_up((size_t)6 * p.bpanel * p.ldk, 256) + round_up((size_t)6 * p.mpanel * p.ldk, 256) +
                     round_up((size_t)(vsplit * p.vgroup), 256);
+    return true;
 }
 
 static hipError_t x3_apply(const ApplyPlan& p, const float* U, const float* s, const float* V, const float* X,

@@ -354,9 +354,9 @@ int lrc_matrix_apply_noalloc(const void* U, const void* s, const void* V, const 
     int rc = check_apply_arrays(U, s, V, X, Y, m, n, k, batch, prec);
     if (rc) return rc;
     ApplyPlan plan = plan_apply(m, n, k, batch, prec, g_force_path, U, V, X);
-    if (plan.x3) x3_panels(plan, m, batch, (size_t)LRC_NOALLOC_SCRATCH_BYTES);
     const size_t need = plan.scratch_bytes;
-    if (need > (size_t)LRC_NOALLOC_SCRATCH_BYTES)
+    if (need > (size_t)LRC_NOALLOC_SCRATCH_BYTES ||
+        (plan.x3 && !x3_panels(plan, m, batch, (size_t)LRC_NOALLOC_SCRATCH_BYTES)))
         return fail(LRC_EINVAL, "this apply needs %zu bytes of scratch, above the %lld of the allocation-free entry",
                     need, (long long)LRC_NOALLOC_SCRATCH_BYTES);
     int dev;

@@ -78,8 +78,10 @@ struct ApplyPlan {
 ApplyPlan plan_apply(int64_t m, int64_t n, int64_t k, int64_t b, int prec, int path, const void* U = nullptr,
                      const void* V = nullptr, const void* X = nullptr);
 size_t apply_workspace_bytes(const ApplyPlan& p);
-// Cuts the panels of a split plan (p.x3) to `limit` bytes of scratch.
-void x3_panels(ApplyPlan& p, int64_t m, int64_t b, size_t limit);
+// Cuts the panels of a split plan (p.x3) to `limit` bytes of scratch; false
+// when they do not fit.  Plans whose scratch_bytes the allocation-free entry
+// takes always fit its scratch.
+bool x3_panels(ApplyPlan& p, int64_t m, int64_t b, size_t limit);
 
 hipError_t launch_apply(const ApplyPlan& p, const void* U, const void* s, const void* V,
                         const void* X, void* Y, int64_t m, int64_t n, int64_t k, int64_t b,

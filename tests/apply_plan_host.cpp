@@ -1,0 +1,58 @@
+// Host sweep over apply plans (no GPU): every FP32 call whose scratch_bytes the
+// allocation-free entry takes must fit its scratch in the plan that runs.
+// Built and run by test_apply_plan_host.py; prints the plans that do not fit.
+#include <algorithm>
+#include <cmath>
+#include <cstdio>
+#include <random>
+
+#include "../include/lrc.h"
+#include "../paper_2607_12969_amd/csrc/lrc_internal.h"
+
+using namespace lrc;
+
+namespace {
+const size_t kLimit = (size_t)LRC_NOALLOC_SCRATCH_BYTES;
+int bad = 0;
+long split = 0, cut = 0;
+
+void check(int64_t m, int64_t n, int64_t k, int64_t b) {
+    if (k > std::min(m, n)) return;
+    const void* p = reinterpret_cast<const void*>((uintptr_t)0x10000);
+    ApplyPlan plan = plan_apply(m, n, k, b, P32, 0, p, p, p);
+    if (plan.scratch_bytes > kLimit) return;
+    if (plan.x3) {
+        ++split;
+        cut += apply_workspace_bytes(plan) > kLimit;
+        x3_panels(plan, m, b, kLimit);
+    }
+    const size_t need = apply_workspace_bytes(plan);
+    if (need > kLimit || (plan.x3 && (plan.bpanel < 1 || plan.mpanel < 1 || plan.vgroup < 1))) {
+        ++bad;
+        std::printf("%lld x %lld k %lld b %lld: %zu of %zu\n", (long long)m, (long long)n, (long long)k, (long long)b,
+                    need, kLimit);
+    }
+}
+}  // namespace
+
+int main() {
+    // one split of the planes of V just above a quarter of the scratch
+    check(8194, 47657, 332, 5388);
+    check(8029, 47634, 336, 5560);
+    check(292436, 103217, 352, 7104);
+    check(47631, 47631, 336, 8192);
+    std::mt19937_64 rng(1);
+    auto size = [&](double lo, double hi) {
+        return (int64_t)std::exp(std::uniform_real_distribution<double>(std::log(lo), std::log(hi))(rng));
+    };
+    for (int i = 0; i < 400000; ++i) check(size(128, 400000), size(16, 400000), size(1, 5000), size(512, 60000));
+    // splits at the largest bytes of V's planes: n a multiple of what fills them
+    for (int64_t k = 17; k <= 4400; k += 5)
+        for (int64_t q = 1; q <= 12; ++q) {
+            const int64_t kpad = round_up(k, 16) + 16, n = q * ((int64_t)(16 << 20) / (6 * kpad));
+            for (int64_t b : {512, 1024, 4096, 8192})
+                for (int64_t m : {4400, 65536}) check(m, n + (k & 31), k, b);
+        }
+    std::printf("%ld split plans, %ld cut to panels, %d do not fit\n", split, cut, bad);
+    return bad ? 1 : (split > 1000 && cut > 100 ? 0 : 2);
+}

@@ -363,3 +363,16 @@ def test_fp32_split_subnormal_columns(lrc):
     ref = U.astype(np.float64) @ (s.astype(np.float64)[:, None] * (V.astype(np.float64).T @ X.astype(np.float64)))
     for cols in (slice(0, 4000), tiny, slice(4100, 4101), slice(4300, b)):
         assert rel_fro(Y[:, cols], ref[:, cols]) <= TOL["fp32"]
+
+
+def test_fp32_split_panels_at_the_scratch_limit(lrc):
+    """A size whose smallest piece of V's planes is just above a quarter of the
+    allocation-free scratch: accepted by both entries, with equal bits."""
+    import torch
+    m, n, k, b = 8194, 47657, 332, 5388
+    g = torch.Generator(device="cuda").manual_seed(5)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")   # noqa: E731
+    args = rnd(m, k) / 90, torch.rand(k, generator=g, device="cuda"), rnd(n, k) / 200, rnd(n, b)
+    out = torch.full((m, b), float("nan"), device="cuda")
+    lrc.matrix_apply_noalloc(*args, out)
+    assert torch.equal(out, lrc.matrix_apply(*args))
