@@ -1155,7 +1155,7 @@ size_t apply_workspace_bytes(const ApplyPlan& p) {
 }
 
 ApplyPlan plan_apply(int64_t m, int64_t n, int64_t k, int64_t b, int prec, int path, const void* U,
-                     const void* V, const void* X) {
+                     const void* V, const void* X, bool split) {
     ApplyPlan p{};
     if (path != 1 && path != 2) path = (b <= kStreamMaxBatch) ? 1 : 2;
     if (path == 1 && b > kStreamMaxBatch) path = 2;
@@ -1266,7 +1266,7 @@ ApplyPlan plan_apply(int64_t m, int64_t n, int64_t k, int64_t b, int prec, int p
         if (small_takes(m, n, k, b)) {
             p.small = 1;
             p.part_bytes = p.mid_bytes = p.stage_bytes = 0;
-        } else if (x3_takes(m, n, k, b, prec, U, V, X)) {
+        } else if (split && x3_takes(m, n, k, b, prec, U, V, X)) {
             ApplyPlan q = p;
             if (x3_plan(q, m, n, k, b)) p = q;
         }

@@ -251,6 +251,7 @@ hipError_t Workspace::reserve(size_t bytes, hipStream_t stream) {
         hipError_t e = hipMalloc(reinterpret_cast<void**>(&base), want);
         if (e != hipSuccess) {
             base = nullptr;
+            (void)hipGetLastError();   // reported here; a later launch check must not see it
             return e;
         }
         cap = want;
@@ -384,7 +385,9 @@ int lrc_matrix_apply(const void* U, const void* s, const void* V, const void* X,
     ApplyPlan plan = plan_apply(m, n, k, batch, prec, g_force_path, U, V, X);
     Workspace& ws = workspace_for(dev, st);
     ws.reset();
-    hipError_t he = ws.reserve(apply_workspace_bytes(plan), st);
+    hipError_t he = reserve_apply(
+        plan, m, batch, [&](size_t bytes) { return ws.reserve(bytes, st); },
+        [&] { return plan_apply(m, n, k, batch, prec, g_force_path, U, V, X, false); });
     if (he != hipSuccess) return fail_hip(he, "workspace");
     he = launch_apply(plan, U, s, V, X, Y, m, n, k, batch, prec, ws, st);
     if (he != hipSuccess) return fail_hip(he, "apply launch");

@@ -76,12 +76,24 @@ struct ApplyPlan {
 
 // U, V, X are only inspected for alignment (may be null).
 ApplyPlan plan_apply(int64_t m, int64_t n, int64_t k, int64_t b, int prec, int path, const void* U = nullptr,
-                     const void* V = nullptr, const void* X = nullptr);
+                     const void* V = nullptr, const void* X = nullptr, bool split = true);
 size_t apply_workspace_bytes(const ApplyPlan& p);
 // Cuts the panels of a split plan (p.x3) to `limit` bytes of scratch; false
 // when they do not fit.  Plans whose scratch_bytes the allocation-free entry
 // takes always fit its scratch.
 bool x3_panels(ApplyPlan& p, int64_t m, int64_t b, size_t limit);
+// Workspace of a call by `reserve(bytes)`.  A split plan takes up to 1 GiB; when
+// that is not to be had it is cut to panels within the workspace of the plan
+// `general()` without the split (the same output bits), and where those do not
+// fit that plan takes its place.
+template <class Reserve, class General>
+hipError_t reserve_apply(ApplyPlan& p, int64_t m, int64_t b, Reserve&& reserve, General&& general) {
+    hipError_t e = reserve(apply_workspace_bytes(p));
+    if (e != hipErrorOutOfMemory || !p.x3) return e;
+    const ApplyPlan g = general();
+    if (!x3_panels(p, m, b, apply_workspace_bytes(g))) p = g;
+    return reserve(apply_workspace_bytes(p));
+}
 
 hipError_t launch_apply(const ApplyPlan& p, const void* U, const void* s, const void* V,
                         const void* X, void* Y, int64_t m, int64_t n, int64_t k, int64_t b,

@@ -1,9 +1,13 @@
-// Host sweep over apply plans (no GPU): every FP32 call whose scratch_bytes the
-// allocation-free entry takes must fit its scratch in the plan that runs.
-// Built and run by test_apply_plan_host.py; prints the plans that do not fit.
+// Host sweeps over apply plans (no GPU), built and run by
+// test_apply_plan_host.py; each prints the plans that fail it.
+//   scratch  every FP32 call whose scratch_bytes the allocation-free entry takes
+//            fits its scratch in the plan that runs
+//   memory   where only the memory of the plan without the split is free, the
+//            split's reservation still succeeds within it
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
+#include <cstring>
 #include <random>
 
 #include "../include/lrc.h"
@@ -16,7 +20,38 @@ const size_t kLimit = (size_t)LRC_NOALLOC_SCRATCH_BYTES;
 int bad = 0;
 long split = 0, cut = 0;
 
-void check(int64_t m, int64_t n, int64_t k, int64_t b) {
+void failed(int64_t m, int64_t n, int64_t k, int64_t b, size_t need, size_t limit) {
+    ++bad;
+    std::printf("%lld x %lld k %lld b %lld: %zu of %zu\n", (long long)m, (long long)n, (long long)k, (long long)b, need,
+                limit);
+}
+
+void memory(int64_t m, int64_t n, int64_t k, int64_t b) {
+    if (k > std::min(m, n)) return;
+    const void* p = reinterpret_cast<const void*>((uintptr_t)0x10000);
+    const ApplyPlan whole = plan_apply(m, n, k, b, P32, 0, p, p, p);
+    const auto general = [&] { return plan_apply(m, n, k, b, P32, 0, p, p, p, false); };
+    const size_t full = apply_workspace_bytes(whole), least = apply_workspace_bytes(general());
+    split += whole.x3;
+    for (size_t room : {full, (full + least) / 2, least}) {
+        ApplyPlan plan = whole;
+        size_t got = 0;
+        int calls = 0;
+        const hipError_t e = reserve_apply(
+            plan, m, b,
+            [&](size_t bytes) {
+                ++calls;
+                got = bytes;
+                return bytes <= room ? hipSuccess : hipErrorOutOfMemory;
+            },
+            general);
+        if (e != hipSuccess || got != apply_workspace_bytes(plan) || (room >= full && calls != 1))
+            failed(m, n, k, b, got, room);
+        cut += calls > 1;
+    }
+}
+
+void scratch(int64_t m, int64_t n, int64_t k, int64_t b) {
     if (k > std::min(m, n)) return;
     const void* p = reinterpret_cast<const void*>((uintptr_t)0x10000);
     ApplyPlan plan = plan_apply(m, n, k, b, P32, 0, p, p, p);
@@ -27,15 +62,14 @@ void check(int64_t m, int64_t n, int64_t k, int64_t b) {
         x3_panels(plan, m, b, kLimit);
     }
     const size_t need = apply_workspace_bytes(plan);
-    if (need > kLimit || (plan.x3 && (plan.bpanel < 1 || plan.mpanel < 1 || plan.vgroup < 1))) {
-        ++bad;
-        std::printf("%lld x %lld k %lld b %lld: %zu of %zu\n", (long long)m, (long long)n, (long long)k, (long long)b,
-                    need, kLimit);
-    }
+    if (need > kLimit || (plan.x3 && (plan.bpanel < 1 || plan.mpanel < 1 || plan.vgroup < 1)))
+        failed(m, n, k, b, need, kLimit);
 }
 }  // namespace
 
-int main() {
+int main(int argc, char** argv) {
+    if (argc != 2) return 3;
+    const auto check = std::strcmp(argv[1], "scratch") == 0 ? scratch : memory;
     // one split of the planes of V just above a quarter of the scratch
     check(8194, 47657, 332, 5388);
     check(8029, 47634, 336, 5560);
@@ -53,6 +87,6 @@ int main() {
             for (int64_t b : {512, 1024, 4096, 8192})
                 for (int64_t m : {4400, 65536}) check(m, n + (k & 31), k, b);
         }
-    std::printf("%ld split plans, %ld cut to panels, %d do not fit\n", split, cut, bad);
+    std::printf("%ld split plans, %ld cut, %d do not fit\n", split, cut, bad);
     return bad ? 1 : (split > 1000 && cut > 100 ? 0 : 2);
 }

@@ -3,6 +3,8 @@ against the library sweeps sizes through plan_apply."""
 import os
 import subprocess
 
+import pytest
+
 from paper_2607_12969_amd import lrc
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -18,8 +20,11 @@ def build_host(tmp_path, source):
     return exe
 
 
-def test_plans_fit_the_allocation_free_scratch(tmp_path):
-    """Every FP32 call that the allocation-free entry accepts fits its scratch."""
-    r = subprocess.run([build_host(tmp_path, "apply_plan_host.cpp")], capture_output=True, text=True, timeout=300)
+@pytest.mark.parametrize("sweep", ["scratch", "memory"])
+def test_plans_fit(tmp_path, sweep):
+    """Every FP32 call that the allocation-free entry accepts fits its scratch;
+    and every call still runs where only the memory of the plan without the
+    split is free."""
+    r = subprocess.run([build_host(tmp_path, "apply_plan_host.cpp"), sweep], capture_output=True, text=True, timeout=300)
     print(r.stdout[-2000:])
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
