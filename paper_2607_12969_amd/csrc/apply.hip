@@ -1797,16 +1797,13 @@ hipError_t launch_gemm_nt(const double* W, int64_t ldw, int64_t nw, const double
     });
 }
 
-// out[c][j] = sum_k A[k][c] Q[k][j] for at most 96 columns of Q (F fragments of
-// 16) and at least 32768 of A: both operands have the product's K as their
-// row index, so the fragments are read straight from memory.  A wave takes
-// 64 columns of A, lane (g, c) the pairs n0 + 2 c and n0 + 32 + 2 c of row k
-// + g, and all of Q, which the caches hold; nothing is shared and nothing
-// waits.  114688 columns, K = 512, 74 of Q: 209 us (64 x 64 tiles, half of the
-// second one idle: 267; matrix cores alone: 120).  With fewer columns there
-// are too few waves for the chip (32768: 512) and the split tiles below take
-// over.
-constexpr int64_t kSlimTnCols = 32768;
+// out[c][j] = sum_k A[k][c] Q[k][j] for few columns of Q (F fragments of 16)
+// and many of A: both operands have the product's K as their row index, so the
+// fragments are read straight from memory.  A wave takes 64 columns of A, lane
+// (g, c) the pairs n0 + 2 c and n0 + 32 + 2 c of row k + g, and all of Q, which
+// the caches hold; nothing is shared and nothing waits.  114688 columns, K =
+// 512, 74 of Q: 199 us (64 x 64 tiles, half of the second one idle: 258; matrix
+// cores alone: 120).
 template <int F>
 __global__ __launch_bounds__(256, 2) void k_tn_slim(const double* __restrict__ Q, int64_t ldq, int nq,
                                                     const double* __restrict__ A, int64_t lda, int64_t cols, int64_t K,
@@ -1829,7 +1826,7 @@ __global__ __launch_bounds__(256, 2) void k_tn_slim(const double* __restrict__ Q
     for (int h = 0; h < 4; ++h)
 #pragma unroll
         for (int f = 0; f < F; ++f) acc[h][f] = zero_accv<double4_t>();
-    constexpr int DA = F > 5 ? 2 : 4;   // steps of A under way (memory), one of Q (cache)
+    constexpr int DA = 4;   // steps of A under way (memory), one of Q (cache)
     double2 xa[DA][2];
     double xq[2][F];
     auto fetch_a = [&](double2(&d)[2], int64_t k0) {
@@ -1882,17 +1879,30 @@ __global__ __launch_bounds__(256, 2) void k_tn_slim(const double* __restrict__ Q
         }
 }
 
+// Where it pays, on the grid K in {256, 512, 1024, 2048, 8192}, 32768 to 114688
+// columns, 12 to 96 of Q, against the split tiles.  It has one workgroup per 256
+// columns and does not split K, so the share of the compute units that its last
+// round of workgroups fills decides: 74 of Q (tiles of 64 leave 54 of 128 rows
+// idle) 0.71 to 0.99 of their time from three quarters on, below it up to 1.39 times;
+// 12 and 20 of Q 0.55 to 0.95 from seven eighths on with K up to 1024 (2048 x 400000
+// and 8192 x 65536: 1.07).  33 to 64 of Q fill the tiles and lose (up to 2.1 times), 81 and
+// more gain less (0.9 to 1.07) than the runs of different K differ.
+bool tn_slim_takes(int64_t nq, int64_t cols, int64_t K) {
+    const int64_t wgs = tiles_of(cols, 256), rounds = tiles_of(wgs, 256);
+    const double fill = (double)wgs / (256.0 * rounds);
+    if (nq > 64 && nq <= 80) return fill >= 0.75;
+    return nq <= 32 && K <= 1024 && fill >= 0.875;
+}
+
 template <int F>
 static void tn_slim(const double* Q, int64_t ldq, int nq, const double* A, int64_t lda, int64_t cols, int64_t K,
                     double* out, int64_t ldo, int mout, hipStream_t st) {
-    if constexpr (F < 6) {
-        if (mout > 16 * F) return tn_slim<F + 1>(Q, ldq, nq, A, lda, cols, K, out, ldo, mout, st);
-    }
     hipLaunchKernelGGL(k_tn_slim<F>, dim3((unsigned)((cols + 255) / 256)), dim3(256), 0, st, Q, ldq, nq, A, lda, cols,
                        K, out, ldo, mout);
 }
 
 size_t gemm_tn_workspace_bytes(int64_t nq, int64_t cols, int64_t K) {
+    if (tn_slim_takes(nq, cols, K)) return 0;
     const int64_t tiles = tiles_of(nq, GramC::BM) * tiles_of(cols, GramC::BN);
     int sp;
     int64_t ch;
@@ -1904,11 +1914,13 @@ hipError_t launch_gemm_tn(const double* Q, int64_t ldq, int64_t nq, const double
                           int64_t K, double* out, int64_t ldo, int64_t mout, Workspace& ws, hipStream_t stream,
                           const char* label, const char* finish_label) {
     const int tm = (int)tiles_of(nq, GramC::BM), tn = (int)tiles_of(cols, GramC::BN);
-    if (!vec_ok<double>(Q, ldq) || !vec_ok<double>(A, lda) || mout < nq || mout > (int64_t)tm * GramC::BM)
+    if (!vec_ok<double>(Q, ldq) || !vec_ok<double>(A, lda) || mout < nq || mout > round_up(nq, 16))
         return hipErrorInvalidValue;
-    if (mout <= 96 && cols >= kSlimTnCols) {
+    if (tn_slim_takes(nq, cols, K)) {
         KernelTimer t(label, stream);
-        tn_slim<1>(Q, ldq, (int)nq, A, lda, cols, K, out, ldo, (int)mout, stream);
+        if (nq <= 16) tn_slim<1>(Q, ldq, (int)nq, A, lda, cols, K, out, ldo, (int)mout, stream);
+        else if (nq <= 32) tn_slim<2>(Q, ldq, (int)nq, A, lda, cols, K, out, ldo, (int)mout, stream);
+        else tn_slim<5>(Q, ldq, (int)nq, A, lda, cols, K, out, ldo, (int)mout, stream);
         return hipGetLastError();
     }
     int sp;

@@ -131,7 +131,9 @@ hipError_t launch_gemm_nt(const double* W, int64_t ldw, int64_t nw, const double
                           int64_t K, const double* svals, double* out, int64_t ldo, int64_t mout, Workspace& ws,
                           hipStream_t stream, const char* label);
 // out[c][j] = sum_{i<K} Q[i][j] A[i][c] for c < cols, j < nq; zero for
-// nq <= j < mout.  Same operand rules.
+// nq <= j < mout (mout at most nq rounded up to 16).  Same operand rules.
+// tn_slim_takes: by the kernel that needs no workspace.
+bool tn_slim_takes(int64_t nq, int64_t cols, int64_t K);
 size_t gemm_tn_workspace_bytes(int64_t nq, int64_t cols, int64_t K);
 hipError_t launch_gemm_tn(const double* Q, int64_t ldq, int64_t nq, const double* A, int64_t lda, int64_t cols,
                           int64_t K, double* out, int64_t ldo, int64_t mout, Workspace& ws, hipStream_t stream,

@@ -106,8 +106,8 @@ def test_rsvd_every_jacobi_block_count(lrc, l):
 
 @pytest.mark.parametrize("m,n,l", [(37, 32768, 5), (101, 32770, 22), (80, 32831, 47), (131, 33001, 96), (90, 32767, 65)])
 def test_rsvd_wide_matrix(lrc, m, n, l):
-    """A^T Q straight from memory (32768 columns and more): ragged tiles of 64
-    columns, odd widths, rows past a multiple of the K step; one width below it."""
+    """A^T Q and the sketch of wide matrices: ragged tiles of 64 columns, odd
+    widths, rows past a multiple of the K step."""
     l = min(l, m)
     A = _power_law(m, n, m, l, expo=1.0)
     Om = synth.test_vectors(l, n, l)
@@ -115,6 +115,27 @@ def test_rsvd_wide_matrix(lrc, m, n, l):
     k = l - 2
     Uo, so, Vto = O.randomized_svd(A, Om, k + 1, 0)
     _compare_rsvd(_gpu_rsvd(lrc, A, Om, k, 0), (Uo[:, :k], so[:k], Vto[:k]), (m, n, l), so[k])
+
+
+@pytest.mark.parametrize("m,n,l", [(37, 57400, 5), (101, 65471, 22), (33, 65536, 32), (90, 50001, 66), (131, 49153, 80)])
+def test_rsvd_projection_from_memory(lrc, m, n, l):
+    """A^T Q straight from memory (sizes that fill the chip with one workgroup per
+    256 columns): ragged tiles of 64 columns, odd widths, rows past a multiple of
+    the K step, one, two and five fragments."""
+    A = _power_law(m, n, m, l, expo=1.0)
+    Om = synth.test_vectors(l, n, l)
+    print(f"rsvd from memory m={m} n={n} l={l}", flush=True)
+    k = l - 2
+    lrc.profile_reset()
+    lrc.profile_enable(True)
+    try:
+        got = _gpu_rsvd(lrc, A, Om, k, 0)
+        labels = set(lrc.profile_read())
+    finally:
+        lrc.profile_enable(False)
+    assert "factor_project_f64" in labels and "factor_project_finish_f64" not in labels
+    Uo, so, Vto = O.randomized_svd(A, Om, k + 1, 0)
+    _compare_rsvd(got, (Uo[:, :k], so[:k], Vto[:k]), (m, n, l), so[k])
 
 
 @pytest.mark.parametrize("scale", [2.0 ** -300, 2.0 ** 300])
