@@ -1728,13 +1728,16 @@ static void split_plan(int64_t tiles, int64_t K, int* splits, int64_t* chunk, in
     *splits = (int)((K + *chunk - 1) / *chunk);
 }
 
-// At most 96 rows of W (the factorization's sketches and small factors) take
+// At most 80 rows of W (the factorization's sketches and small factors) take
 // one tile of as many fragments as W has, so that no wave has idle ones (the
-// wave's loop then has no guards); wider W takes the 64 x 64 tiles.  74 x
-// 512 over K = 114688 with the sum of the splits: 224 (96-row tiles, 1536
-// workgroups) -> 196 us.
+// wave's loop then has no guards); 81 to 96 rows take 96-row tiles of three
+// fragments a wave, wider W the 64 x 64 tiles.  74 x 512 over K = 114688 with the
+// sum of the splits: 224 (96-row tiles, 1536 workgroups) -> 196 us.
 template <int F> using SlimC = Cfg<double, 16 * F, 64, 32, 1, 4>;
-// Two of their workgroups share a compute unit: one wave of 512.
+using NarrowC = Cfg<double, 96, 64, 16, 2, 2>;
+// Two workgroups of a slim tile share a compute unit (78 KB of LDS each at five
+// fragments): one wave of 512.  Six fragments take 87 KB, so that only one would
+// fit: 8192 x 32768 with 96 of W 1081 us against 966 with NarrowC.
 template <class C> static constexpr int64_t nt_target() { return C::WM == 1 ? 512 : 1536; }
 
 template <class C>
@@ -1754,7 +1757,7 @@ static auto by_fragments(int64_t nw, Fn&& fn) {
     case 3: return fn(SlimC<3>{});
     case 4: return fn(SlimC<4>{});
     case 5: return fn(SlimC<5>{});
-    case 6: return fn(SlimC<6>{});
+    case 6: return fn(NarrowC{});
     default: return fn(GramC{});
     }
 }

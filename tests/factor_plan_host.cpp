@@ -1,6 +1,6 @@
-// Host check of the product A^T Q's route (no GPU), built and run by
-// test_apply_plan_host.py: the kernel straight from memory only where it was
-// measured to be the faster one, and without a workspace there.
+// Host check of the factorization products' routes (no GPU), built and run by
+// test_apply_plan_host.py: A^T Q straight from memory only where that was
+// measured to be faster, and without a workspace there; the sketch's tiles.
 #include <cstdio>
 
 #include "../paper_2607_12969_amd/csrc/lrc_internal.h"
@@ -41,6 +41,17 @@ int main() {
         if (c.slim ? !slim : !tiles) {
             ++bad;
             std::printf("%lld of %lld columns, K %lld\n", (long long)c.nq, (long long)c.cols, (long long)c.K);
+        }
+    }
+    // A Omega^T for 81 to 96 test vectors: 1536 workgroups of 96-row tiles (six
+    // fragments a wave leave one workgroup per compute unit, 1.05 to 1.19 times
+    // their time), 512 of slim tiles below
+    const int64_t rows = 8192, K = 32768, tiles = rows / 64;
+    for (int64_t nw : {65, 80, 81, 96}) {
+        const int64_t bm = nw > 80 ? 96 : 80, splits = (nw > 80 ? 1536 : 512) / tiles;
+        if (gemm_nt_workspace_bytes(nw, rows, K) != (size_t)(tiles * splits * bm * 64 * 8)) {
+            ++bad;
+            std::printf("sketch of %lld\n", (long long)nw);
         }
     }
     return bad ? 1 : 0;

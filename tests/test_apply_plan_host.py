@@ -30,7 +30,8 @@ def test_plans_fit(tmp_path, sweep):
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
 
 
-def test_projection_route(tmp_path):
-    """A^T Q straight from memory only at the sizes where that was the faster route."""
+def test_factor_routes(tmp_path):
+    """A^T Q straight from memory only at the sizes where that was the faster
+    route; the sketch's tiles by the number of test vectors."""
     r = subprocess.run([build_host(tmp_path, "factor_plan_host.cpp")], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr
