@@ -9,11 +9,15 @@
 // |dropped| <= |a2 b3| + |a3 b2| + |a3 b3| <= 2.01 * 2^-24 |a b| and of either
 // sign.  Six bfloat16 products stand for one FP32 product, with one rounding
 // of the accumulator per 32 K values and term instead of one per 4.
-// The split is exact for 2^-100 <= |x| < 2^62 and for 0.  Operands kept as
-// planes in memory carry NaN for any other value, so that the accumulators
-// it reaches are not finite; operands split on the way are range-checked.
-// Either way the tile is then computed again with the FP32 instruction, so
-// infinities, NaN, overflow and underflow come out as they do there.
+// The split is exact for 2^-100 <= |x| < 2^62 and for 0.  Any other value (of V,
+// U or T': marked by the kernel that writes the planes; of X: checked where it
+// is split) sends the K step that it belongs to, of one wave's columns in phase
+// 1 and of one tile in phase 2, to the FP32 instruction.  So do accumulators that
+// are not finite with all their steps, and infinities, NaN, overflow and underflow
+// come out as they do there.  8192 x 8192, k = 257, b = 4096 takes 212 us, 352 on
+// the FP32 instruction throughout; with 1e-33 in 1e-5 of the values of X, V or U
+// 221 to 225, in 1e-3 of them 298 (U) to 373 (V), in every value of X 472 (phase
+// 1 runs its loop for nothing).
 #pragma once
 
 typedef __bf16 bf2_t __attribute__((ext_vector_type(2)));
@@ -36,10 +40,10 @@ __device__ __forceinline__ void x3_split2(float a, float b, unsigned (&p)[3]) {
     p[2] = __builtin_bit_cast(unsigned, __builtin_convertvector((f2_t){qa, qb}, bf2_t));
 }
 
-// NaN for a value outside the split's range.
-__device__ __forceinline__ float x3_poison(float x) {
+// A value outside the split's range.
+__device__ __forceinline__ bool x3_outside(float x) {
     const float a = __builtin_fabsf(x);
-    return (a < kX3Max && (a >= kX3Min || a == 0.0f)) ? x : __builtin_nanf("");
+    return !(a < kX3Max) | ((a < kX3Min) & (a != 0.0f));   // no branches: loads stay together
 }
 
 // Range of the values split on the way: largest magnitude and smallest
@@ -84,21 +88,24 @@ __device__ __forceinline__ float4_t x3_mfma(bf8_t a, bf8_t b, float4_t c) {
 // ---- planes of U and of V^T, one launch ----------------------------------------
 // Workgroups [0, ublocks) write the planes of U (m x k, [m][ldk]), 256 chunks
 // of 8 values each; the rest write those of V^T ([kpad][ldn] from V, n x k),
-// a 64 x 64 tile each through LDS.  Both zero padded; any alignment.  Bound
-// by their 10 bytes per value: 65536 x 513 and 4096 x 513 in 62 us (5.8 TB/s).
+// a 64 x 64 tile each through LDS.  Both zero padded; any alignment.  Values
+// outside the split's range: umask has one bit per chunk of U, vflag four bytes
+// (one per wave) per 32 rows, one K step, of a tile of V.
+// Bound by their 10 bytes per value: 65536 x 513 and 4096 x 513 in 62 us (5.8 TB/s).
 __global__ __launch_bounds__(256) void k_x3_planes(const float* __restrict__ U, int64_t m, int64_t k,
                                                    unsigned short* __restrict__ Up, int64_t ldk, unsigned ublocks,
                                                    const float* __restrict__ V, int64_t n,
                                                    unsigned short* __restrict__ Vp, int64_t ldn, int64_t kpad,
-                                                   unsigned ntiles) {
+                                                   unsigned ntiles, unsigned long long* __restrict__ umask,
+                                                   unsigned char* __restrict__ vflag) {
     __shared__ float tile[64][65];
     const int tid = threadIdx.x;
     float v[8];
     if (blockIdx.x < ublocks) {
-        const int64_t c = (int64_t)blockIdx.x * 256 + tid, cpr = ldk / 8;
-        if (c >= m * cpr) return;
-        const int64_t i = c / cpr, j0 = (c - i * cpr) * 8;
+        const int64_t c = (int64_t)blockIdx.x * 256 + tid, cpr = ldk / 8, i = std::min(c / cpr, m - 1);
+        const int64_t j0 = (c % cpr) * 8;
         const float* last = U + (m * k - 1);
+        bool out = false;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int64_t j = j0 + 4 * h;
@@ -106,28 +113,42 @@ __global__ __launch_bounds__(256) void k_x3_planes(const float* __restrict__ U, 
             mc.fetch(U + i * k + (j < k ? j : k - 1), last);
             const float4_t w = mc.template value<float4_t>();
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[4 * h + q] = j + q < k ? x3_poison(w[q]) : 0.0f;
+            for (int q = 0; q < 4; ++q) {
+                v[4 * h + q] = j + q < k ? w[q] : 0.0f;
+                out |= x3_outside(v[4 * h + q]);
+            }
         }
-        u32x4_t part[3];
+        if (c < m * cpr) {
+            u32x4_t part[3];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            unsigned p[3];
-            x3_split2(v[2 * q], v[2 * q + 1], p);
+            for (int q = 0; q < 4; ++q) {
+                unsigned p[3];
+                x3_split2(v[2 * q], v[2 * q + 1], p);
 #pragma unroll
-            for (int t = 0; t < 3; ++t) part[t][q] = p[t];
+                for (int t = 0; t < 3; ++t) part[t][q] = p[t];
+            }
+#pragma unroll
+            for (int t = 0; t < 3; ++t) *reinterpret_cast<u32x4_t*>(Up + t * m * ldk + c * 8) = part[t];
         }
-#pragma unroll
-        for (int t = 0; t < 3; ++t) *reinterpret_cast<u32x4_t*>(Up + t * m * ldk + c * 8) = part[t];
+        const unsigned long long mask = __builtin_amdgcn_ballot_w64(out);
+        if ((tid & 63) == 0) umask[c >> 6] = mask;
         return;
     }
     const unsigned b = blockIdx.x - ublocks;
     const int64_t n0 = (int64_t)(b % ntiles) * 64, k0 = (int64_t)(b / ntiles) * 64;
     const int tx = tid & 63, ty = tid >> 6;
+    bool out[2] = {false, false};
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
         const int64_t i = n0 + ty + 4 * u, j = k0 + tx;
         const float x = V[(i < n ? i : n - 1) * k + (j < k ? j : k - 1)];
-        tile[ty + 4 * u][tx] = (i < n && j < k) ? x3_poison(x) : 0.0f;
+        tile[ty + 4 * u][tx] = (i < n && j < k) ? x : 0.0f;
+        out[u / 8] |= x3_outside(x);   // past the edges: of the last row or column once more
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const bool any = __builtin_amdgcn_ballot_w64(out[h]) != 0;
+        if (tx == 0) vflag[8 * (int64_t)b + 4 * h + ty] = any ? 1 : 0;
     }
     __syncthreads();
 #pragma unroll
@@ -158,12 +179,15 @@ __global__ __launch_bounds__(256) void k_x3_planes(const float* __restrict__ U, 
 // copy nor LDS.  Two workgroups per compute unit cover each other's load
 // latency.  Bound by the matrix cores: 8192 x 8192, k = 257, b = 4096 runs in
 // 101 us against 201 us on the FP32 instruction (split operands of both
-// sides through LDS, 64 rank rows per tile: 191 us).
+// sides through LDS, 64 rank rows per tile: 191 us).  A wave leaves out the
+// steps with a value outside the split's range and runs them after the loop on
+// the FP32 instruction.
 template <int NF>
 __global__ __launch_bounds__(256, 2) void k_p1_x3(const unsigned short* __restrict__ Vp, int64_t ldn, int64_t kpad,
                                                   const float* __restrict__ V, int64_t k,
                                                   const float* __restrict__ X, int64_t ldx, int64_t n, int64_t b,
                                                   int64_t chunk, int nf, int tiles_m, int tiles_n, int splits,
+                                                  const unsigned char* __restrict__ vflag,
                                                   float* __restrict__ part) {
     __shared__ alignas(16) unsigned short S[3 * NF * 16 * kX3BK];
     const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
@@ -191,9 +215,14 @@ __global__ __launch_bounds__(256, 2) void k_p1_x3(const unsigned short* __restri
         col[h] = nt * 128 + wave * 32 + h * 16 + r;
         xp[h] = X + (col[h] < b ? col[h] : b - 1);
     }
+    // V's flags over this tile's ranks, four bytes per 64 ranks and step
+    const int64_t kt0 = mrow0 >> 6, nkt = ((mrow0 + nf * 16 - 1) >> 6) - kt0 + 1;
+    const int* vf = reinterpret_cast<const int*>(vflag) + (kt0 + (lane < nkt ? lane : 0)) * (((ldn + 63) >> 6) * 2);
     float xr[2][8];
+    int flag;
     auto fetch = [&](int j) {
         const int64_t row0 = kbeg + (int64_t)j * kX3BK + 8 * g;
+        flag = vf[kbeg / kX3BK + j];
         if (kbeg + (int64_t)(j + 1) * kX3BK <= n) {
 #pragma unroll
             for (int h = 0; h < 2; ++h)
@@ -211,12 +240,16 @@ __global__ __launch_bounds__(256, 2) void k_p1_x3(const unsigned short* __restri
     for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int f = 0; f < NF; ++f) acc[h][f] = zero_accv<float4_t>();
-    X3Range range;
+    unsigned left = 0;   // steps left out of the loop: bit j % 32 of lane j / 32
     move(0);
     fetch(0);
     for (int j = 0; j < nsteps; ++j) {
         wait_loads();
         __syncthreads();
+        bf8_t v[2][3];   // fragment f and, read under its products, f + 1
+#pragma unroll
+        for (int q = 0; q < 3; ++q) v[0][q] = x3_frag(S + q * NF * 16 * kX3BK, 0, lane);
+        X3Range range;
         bf8_t x[2][3];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -232,54 +265,103 @@ __global__ __launch_bounds__(256, 2) void k_p1_x3(const unsigned short* __restri
 #pragma unroll
             for (int t = 0; t < 3; ++t) x[h][t] = __builtin_bit_cast(bf8_t, pk[t]);
         }
+        const bool skip = __builtin_amdgcn_ballot_w64(flag != 0 || range.bad()) != 0;
+        if (skip && lane == (j >> 5)) left |= 1u << (j & 31);
         if (j + 1 < nsteps) fetch(j + 1);
-        bf8_t v[2][3];   // fragment f and, read under its products, f + 1
+        if (!skip) {
 #pragma unroll
-        for (int q = 0; q < 3; ++q) v[0][q] = x3_frag(S + q * NF * 16 * kX3BK, 0, lane);
+            for (int f = 0; f < NF; ++f) {
+                if (f < nf) {
+                    if (f + 1 < NF) {
 #pragma unroll
-        for (int f = 0; f < NF; ++f) {
-            if (f < nf) {
-                if (f + 1 < NF) {
+                        for (int q = 0; q < 3; ++q)
+                            v[(f + 1) & 1][q] = x3_frag(S + q * NF * 16 * kX3BK, (f + 1) * 16, lane);
+                    }
 #pragma unroll
-                    for (int q = 0; q < 3; ++q)
-                        v[(f + 1) & 1][q] = x3_frag(S + q * NF * 16 * kX3BK, (f + 1) * 16, lane);
+                    for (int t = 0; t < 6; ++t)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h) acc[h][f] = x3_mfma(v[f & 1][kX3A[t]], x[h][kX3B[t]], acc[h][f]);
                 }
-#pragma unroll
-                for (int t = 0; t < 6; ++t)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) acc[h][f] = x3_mfma(v[f & 1][kX3A[t]], x[h][kX3B[t]], acc[h][f]);
             }
         }
         __syncthreads();
         if (j + 1 < nsteps) move(j + 1);
     }
-    bool bad = range.bad();
+    // The steps left out, on the FP32 instruction, operands straight from
+    // memory: V requested one row per lane group ahead of its products, X four,
+    // also from one step to the next.  Where the sums are not finite, all steps
+    // once more that way.
+    const unsigned m1 = (unsigned)(mrow0 + r), mk = (unsigned)(k - 1);
+    for (bool all = false;;) {
+        int word = -1;
+        unsigned bits = 0;
+        auto next = [&]() -> int64_t {   // first row of the next step left out, or -1
+            while (bits == 0) {
+                if (++word * 32 >= nsteps) return -1;
+                bits = __builtin_amdgcn_readlane(left, word);
+            }
+            const int j = word * 32 + __builtin_ctz(bits);
+            bits &= bits - 1;
+            return kbeg + (int64_t)j * kX3BK;
+        };
+        float vn[NF], xn[4][2];
+        auto get_v = [&](int64_t row) {
+            const float* p = V + (row < n ? row : n - 1) * k;
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+            for (int f = 0; f < NF; ++f)   // ranks past k: sums that nothing reads
+                if (f < nf) vn[f] = p[std::min(m1 + f * 16, mk)];
+        };
+        auto get_x = [&](int u, int64_t row) {
 #pragma unroll
-        for (int f = 0; f < NF; ++f)
+            for (int h = 0; h < 2; ++h) xn[u][h] = xp[h][(row < n ? row : n - 1) * ldx];
+        };
+        int64_t cur = next();
+        if (cur >= 0) {
+            get_v(cur + g);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) bad = bad || !(__builtin_fabsf(acc[h][f][v]) < __builtin_inff());
-    if (__syncthreads_or(bad ? 1 : 0)) {
-        // FP32 instruction, operands straight from memory
+            for (int u = 0; u < 4; ++u) get_x(u, cur + 4 * u + g);
+        }
+        while (cur >= 0) {
+            const int64_t nxt = next(), nb = nxt >= 0 ? nxt : cur;
+#pragma clang loop unroll(disable)
+            for (int half = 0; half < 2; ++half) {
+                const int64_t here = cur + 16 * half, then = half == 0 ? cur + 16 : nb;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const bool in = here + 4 * u + g < n;
+                    float vc[NF], xc[2];
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) vc[f] = in ? vn[f] : 0.0f;
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) xc[h] = in ? xn[u][h] : 0.0f;
+                    get_v((u < 3 ? here + 4 * (u + 1) : then) + g);
+                    get_x(u, then + 4 * u + g);
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) {
+                        if (f < nf) {
+                            acc[0][f] = mfma(vc[f], xc[0], acc[0][f]);
+                            acc[1][f] = mfma(vc[f], xc[1], acc[1][f]);
+                        }
+                    }
+                }
+            }
+            cur = nxt;
+        }
+        bool bad = false;
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) bad = bad || !(__builtin_fabsf(acc[h][f][v]) < __builtin_inff());
+        if (__builtin_amdgcn_ballot_w64(bad) == 0 || all) break;
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
             for (int f = 0; f < NF; ++f) acc[h][f] = zero_accv<float4_t>();
-        for (int64_t i0 = kbeg; i0 < kend; i0 += 4) {
-            const bool in = i0 + g < kend;
-            const int64_t i = in ? i0 + g : kend - 1;
-            const float x0 = in ? xp[0][i * ldx] : 0.0f, x1 = in ? xp[1][i * ldx] : 0.0f;
-#pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                if (f < nf) {
-                    const int64_t mm = mrow0 + f * 16 + r;
-                    const float v = (in && mm < k) ? V[i * k + mm] : 0.0f;
-                    acc[0][f] = mfma(v, x0, acc[0][f]);
-                    acc[1][f] = mfma(v, x1, acc[1][f]);
-                }
-            }
-        }
+        const int mine = nsteps - 32 * lane;
+        left = mine >= 32 ? ~0u : mine > 0 ? (1u << mine) - 1u : 0u;
+        all = true;
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -293,16 +375,17 @@ __global__ __launch_bounds__(256, 2) void k_p1_x3(const unsigned short* __restri
 
 // T'^T[c][j] = s_j * (sum of the split partials in split order), as FP32
 // (pitch ldt) and as planes (pitch ldk), zeros for j >= k: one thread per four
-// consecutive j.
+// consecutive j.  tmask: one bit per thread, set for a value outside the split's
+// range.
 __global__ __launch_bounds__(256) void k_x3_finish(const float* __restrict__ part, int64_t kpad, int splits,
                                                    const float* __restrict__ s, int64_t k, int64_t b,
                                                    float* __restrict__ Tt, int64_t ldt,
-                                                   unsigned short* __restrict__ Tp, int64_t ldk) {
+                                                   unsigned short* __restrict__ Tp, int64_t ldk,
+                                                   unsigned long long* __restrict__ tmask) {
     const int64_t per = ldk / 4, idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= b * per) return;
     const int64_t c = idx / per, j = (idx - c * per) * 4;
     float4_t sum = zero_accv<float4_t>();
-    if (j < k) {
+    if (c < b && j < k) {
         const float* src = part + c * kpad + j;
         const int64_t qs = b * kpad;
         int q = 0;
@@ -317,10 +400,14 @@ __global__ __launch_bounds__(256) void k_x3_finish(const float* __restrict__ par
 #pragma unroll
         for (int v = 0; v < 4; ++v) sum[v] = j + v < k ? s[j + v] * sum[v] : 0.0f;
     }
+    const unsigned long long mask = __builtin_amdgcn_ballot_w64(x3_outside(sum[0]) | x3_outside(sum[1]) |
+                                                                x3_outside(sum[2]) | x3_outside(sum[3]));
+    if ((threadIdx.x & 63) == 0) tmask[idx >> 6] = mask;
+    if (c >= b) return;
     if (j < ldt) *reinterpret_cast<float4_t*>(Tt + c * ldt + j) = sum;
     unsigned lo[3], hi[3];
-    x3_split2(x3_poison(sum[0]), x3_poison(sum[1]), lo);
-    x3_split2(x3_poison(sum[2]), x3_poison(sum[3]), hi);
+    x3_split2(sum[0], sum[1], lo);
+    x3_split2(sum[2], sum[3], hi);
 #pragma unroll
     for (int t = 0; t < 3; ++t) *reinterpret_cast<u32x2_t*>(Tp + t * b * ldk + c * ldk + j) = (u32x2_t){lo[t], hi[t]};
 }
@@ -330,8 +417,11 @@ __global__ __launch_bounds__(256) void k_x3_finish(const float* __restrict__ par
 // workgroup of 4 waves.  A K step of 32 moves 48 KB of planes straight into
 // LDS; every wave reads its 24 fragments into registers, and the next step's
 // loads run under the 96 products of this one (one LDS buffer, two
-// workgroups per compute unit).  Tiles whose accumulators are not finite are
-// computed again from the FP32 operands (U in place, T'^T with pitch ldt).
+// workgroups per compute unit).  K steps with a marked value of U or T' are left
+// out of the loop and run after it from the FP32 operands (U in place, T'^T with
+// pitch ldt) on the FP32 instruction; a tile with more than half of its steps
+// marked, or a mark among more than 64, or sums that are not finite, runs all
+// of them that way.
 // Bound by the matrix cores at the clock that their power leaves (1.6 to 1.8
 // of 2.4 GHz here): 65536 x 4096, k = 513, b = 4096 in 1370 to 1550 us against
 // 2160 us on the FP32 instruction; 8192 x 8192, k = 257 in 103 against 168 us.
@@ -343,10 +433,13 @@ __global__ __launch_bounds__(256, 2) void k_p2_x3(const unsigned short* __restri
                                                   const unsigned short* __restrict__ Tp, int64_t ldk,
                                                   const float* __restrict__ U, int64_t M, int64_t k,
                                                   const float* __restrict__ Tt, int64_t ldt, int64_t N, int tiles_m,
-                                                  int tiles_n, float* __restrict__ Y, int64_t ldy, int vec16) {
+                                                  int tiles_n, const unsigned long long* __restrict__ umask,
+                                                  const unsigned long long* __restrict__ tmask, float* __restrict__ Y,
+                                                  int64_t ldy, int vec16) {
     using C = X3C2;
     constexpr int PLANE = 128 * kX3BK;
-    static_assert(2 * (C::BM + C::BN) * C::LDK * 4 <= 6 * PLANE * 2, "the FP32 loop and the store fit the planes' LDS");
+    static_assert(2 * (C::BM + C::BN) * C::LDK * 4 <= 6 * PLANE * 2 && (C::BM + C::BN) * 36 * 4 <= 6 * PLANE * 2,
+                  "the FP32 loops and the store fit the planes' LDS");
     __shared__ alignas(16) unsigned short S[6 * PLANE];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -384,37 +477,127 @@ __global__ __launch_bounds__(256, 2) void k_p2_x3(const unsigned short* __restri
             }
     };
     const int nsteps = (int)(ldk / kX3BK);
+    // marks among this tile's rows of U (4 bits per K step of a row) and of T'^T
+    // (8 bits); every wave reads them all, so that they agree without a barrier
+    const int64_t u0 = m0 * (ldk / 8), u1 = std::min(m0 + C::BM, M) * (ldk / 8);
+    const int64_t t0 = n0 * (ldk / 4), t1 = std::min(n0 + C::BN, N) * (ldk / 4);
+    const unsigned long long *um = umask + (u0 >> 6), *tm = tmask + (t0 >> 6);
+    const int ul = (int)(((u1 - 1) >> 6) - (u0 >> 6)), tl = (int)(((t1 - 1) >> 6) - (t0 >> 6));
+    unsigned long long some = 0;   // neighbours' bits included; the first 1000 ranks in one round of loads
+#pragma unroll
+    for (int q = 0; q < 4; ++q) some |= um[std::min(lane + 64 * q, ul)];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) some |= tm[std::min(lane + 64 * q, tl)];
+    for (int i = lane + 256; i <= ul; i += 64) some |= um[i];
+    for (int i = lane + 512; i <= tl; i += 64) some |= tm[i];
     move(0);
-    for (int j = 0; j < nsteps; ++j) {
-        wait_loads();
-        __syncthreads();
-        bf8_t u[C::FM][3], t[C::FN][3];
+    unsigned long long marked = 0;   // K steps with marks
+    bool all = false;                // every step on the FP32 instruction
+    if (__builtin_amdgcn_ballot_w64(some != 0) != 0) {
+        all = nsteps > 64;
+        if (!all) {
+            auto steps = [&](const unsigned long long* mask, int last, int64_t first, int64_t end, int per) {
+                for (int i = lane; i <= last; i += 64) {
+                    const int64_t c0 = ((first >> 6) + i) << 6;
+                    unsigned long long bits = mask[i];
+                    if (c0 < first) bits &= ~0ull << (first - c0);
+                    if (end < c0 + 64) bits &= ~0ull >> (c0 + 64 - end);
+                    for (int j = (int)(c0 / per % nsteps); bits; bits >>= per) {
+                        if (bits & ((1 << per) - 1)) marked |= 1ull << j;
+                        j = j + 1 < nsteps ? j + 1 : 0;
+                    }
+                }
+            };
+            steps(um, ul, u0, u1, 4);
+            steps(tm, tl, t0, t1, 8);
 #pragma unroll
-        for (int q = 0; q < 3; ++q) {
-#pragma unroll
-            for (int fm = 0; fm < C::FM; ++fm) u[fm][q] = x3_frag(S + q * PLANE, wm * C::WTM + fm * 16, lane);
-#pragma unroll
-            for (int fn = 0; fn < C::FN; ++fn) t[fn][q] = x3_frag(S + (3 + q) * PLANE, wn * C::WTN + fn * 16, lane);
+            for (int d = 1; d < 64; d *= 2) marked |= __shfl_xor(marked, d, 64);
+            const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)marked);
+            marked = (unsigned long long)__builtin_amdgcn_readfirstlane((unsigned)(marked >> 32)) << 32 | lo;
+            all = 2 * __builtin_popcountll(marked) > nsteps;
         }
-        __syncthreads();
-        if (j + 1 < nsteps) move(j + 1);
-#pragma unroll
-        for (int e = 0; e < 6; ++e)
-#pragma unroll
-            for (int fn = 0; fn < C::FN; ++fn)
-#pragma unroll
-                for (int fm = 0; fm < C::FM; ++fm)
-                    acc[fn][fm] = x3_mfma(t[fn][kX3A[e]], u[fm][kX3B[e]], acc[fn][fm]);
     }
-    bool bad = false;
-#pragma unroll
-    for (int fn = 0; fn < C::FN; ++fn)
-#pragma unroll
-        for (int fm = 0; fm < C::FM; ++fm)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) bad = bad || !(__builtin_fabsf(acc[fn][fm][v]) < __builtin_inff());
     float* smem = reinterpret_cast<float*>(S);
-    if (__syncthreads_or(bad ? 1 : 0)) {
+    if (!all) {
+        for (int j = 0; j < nsteps; ++j) {
+            wait_loads();
+            __syncthreads();
+            bf8_t u[C::FM][3], t[C::FN][3];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+#pragma unroll
+                for (int fm = 0; fm < C::FM; ++fm) u[fm][q] = x3_frag(S + q * PLANE, wm * C::WTM + fm * 16, lane);
+#pragma unroll
+                for (int fn = 0; fn < C::FN; ++fn) t[fn][q] = x3_frag(S + (3 + q) * PLANE, wn * C::WTN + fn * 16, lane);
+            }
+            __syncthreads();
+            if (j + 1 < nsteps) move(j + 1);
+            if (marked >> (j & 63) & 1) continue;
+#pragma unroll
+            for (int e = 0; e < 6; ++e)
+#pragma unroll
+                for (int fn = 0; fn < C::FN; ++fn)
+#pragma unroll
+                    for (int fm = 0; fm < C::FM; ++fm)
+                        acc[fn][fm] = x3_mfma(t[fn][kX3A[e]], u[fm][kX3B[e]], acc[fn][fm]);
+        }
+        // the marked steps: 128 rows of U and of T'^T as FP32 in LDS, 36 floats apart,
+        // the next step's values requested under the products
+        const int kk = tid & 31, row0 = tid >> 5, q4 = (tid & 7) * 4, row4 = tid >> 3;
+        float uv[16];
+        float4_t tv[4];
+        auto fetch = [&](int64_t k0) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int64_t row = m0 + row0 + 8 * e;
+                uv[e] = U[(row < M ? row : M - 1) * k + (k0 + kk < k ? k0 + kk : k - 1)];
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int64_t row = n0 + row4 + 32 * e;
+                tv[e] = *reinterpret_cast<const float4_t*>(Tt + (row < N ? row : N - 1) * ldt + (k0 + q4 < ldt ? k0 + q4 : 0));
+            }
+        };
+        if (marked) fetch((int64_t)__builtin_ctzll(marked) * kX3BK);
+        while (marked) {
+            const int64_t k0 = (int64_t)__builtin_ctzll(marked) * kX3BK;
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < 16; ++e) smem[(row0 + 8 * e) * 36 + kk] = k0 + kk < k ? uv[e] : 0.0f;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                *reinterpret_cast<float4_t*>(smem + (128 + row4 + 32 * e) * 36 + q4) =
+                    k0 + q4 < ldt ? tv[e] : zero_accv<float4_t>();
+            __syncthreads();
+            marked &= marked - 1;
+            if (marked) fetch((int64_t)__builtin_ctzll(marked) * kX3BK);
+            const float* up = smem + (wm * C::WTM + (lane & 15)) * 36 + (lane >> 4);
+            const float* tp = smem + (128 + wn * C::WTN + (lane & 15)) * 36 + (lane >> 4);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                float u[C::FM], t[C::FN];
+#pragma unroll
+                for (int fm = 0; fm < C::FM; ++fm) u[fm] = up[fm * 16 * 36 + 4 * e];
+#pragma unroll
+                for (int fn = 0; fn < C::FN; ++fn) t[fn] = tp[fn * 16 * 36 + 4 * e];
+#pragma unroll
+                for (int fn = 0; fn < C::FN; ++fn)
+#pragma unroll
+                    for (int fm = 0; fm < C::FM; ++fm) acc[fn][fm] = mfma(t[fn], u[fm], acc[fn][fm]);
+            }
+        }
+        bool bad = false;
+#pragma unroll
+        for (int fn = 0; fn < C::FN; ++fn)
+#pragma unroll
+            for (int fm = 0; fm < C::FM; ++fm)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) bad = bad || !(__builtin_fabsf(acc[fn][fm][v]) < __builtin_inff());
+        all = __syncthreads_or(bad ? 1 : 0) != 0;
+    }
+    if (all) {
+        wait_loads();   // the first step's, which land in the same LDS
+        __syncthreads();
 #pragma unroll
         for (int fn = 0; fn < C::FN; ++fn)
 #pragma unroll
@@ -428,6 +611,7 @@ __global__ __launch_bounds__(256, 2) void k_p2_x3(const unsigned short* __restri
 // About the bytes of V's planes per split and of a column's partial sums; factors
 // too large for both keep the FP32 instruction.  Panels of such sizes fit the
 // allocation-free entry's scratch (x3_plan makes sure).
+constexpr int64_t kX3MaxChunk = (int64_t)64 * 32 * kX3BK;   // rows whose steps fit the bits of a wave's lanes
 constexpr int64_t kX3VBytes = (int64_t)16 << 20, kX3ColBytes = (int64_t)128 << 10;
 
 // Sizes that gain from the split (old and new times on the grid 512 <= m, n <=
@@ -469,11 +653,19 @@ static bool x3_plan(ApplyPlan& p, int64_t m, int64_t n, int64_t k, int64_t b) {
     int64_t splits = std::min((512 + base - 1) / base, n / 128);
     splits = std::min(splits, kX3ColBytes / 4 / p.kpad);
     splits = std::max(splits, (n * p.kpad * 6 + kX3VBytes - 1) / kX3VBytes);
-    if (splits < 1) splits = 1;
+    splits = std::max(splits, (n + kX3MaxChunk - 1) / kX3MaxChunk);
     p.chunk = round_up((n + splits - 1) / splits, kX3BK);
     p.splits = (int)((n + p.chunk - 1) / p.chunk);
     const size_t noalloc = (size_t)LRC_NOALLOC_SCRATCH_BYTES;
     return (p.scratch_bytes > noalloc || x3_panels(p, m, b, noalloc)) && x3_panels(p, m, b, (size_t)1 << 30);
+}
+
+// Bytes of one panel's marks of values outside the split's range (whole workgroups of
+// the kernels that write them).
+static int64_t x3_umask_bytes(const ApplyPlan& p) { return (p.mpanel * (p.ldk / 8) + 255) / 256 * 32; }
+static int64_t x3_tmask_bytes(const ApplyPlan& p) { return (p.bpanel * (p.ldk / 4) + 255) / 256 * 32; }
+static int64_t x3_mark_bytes(const ApplyPlan& p) {
+    return x3_umask_bytes(p) + x3_tmask_bytes(p) + ((p.vgroup * p.chunk + 63) / 64) * ((p.kpad + 63) / 64) * 8;
 }
 
 // Panels within `limit` bytes of scratch: splits whose planes of V^T are held
@@ -482,8 +674,10 @@ static bool x3_plan(ApplyPlan& p, int64_t m, int64_t n, int64_t k, int64_t b) {
 // output value is the same whatever the panels.  False: not even panels of 128
 // columns and rows fit, the plan is not usable.
 bool x3_panels(ApplyPlan& p, int64_t m, int64_t b, size_t limit) {
-    const int64_t vsplit = 6 * p.kpad * p.chunk, col = (int64_t)p.splits * p.kpad * 4 + p.Kp * 4 + 6 * p.ldk;
-    const int64_t row = 6 * p.ldk, room = (int64_t)limit - 4096;
+    // marks included: eight bytes per 64 x 64 of V, a bit per 8 values of U, 4 of T'
+    const int64_t vsplit = 6 * p.kpad * p.chunk + 8 * ((p.chunk + 63) / 64) * ((p.kpad + 63) / 64);
+    const int64_t col = (int64_t)p.splits * p.kpad * 4 + p.Kp * 4 + 6 * p.ldk + p.ldk / 32;
+    const int64_t row = 6 * p.ldk + p.ldk / 64 + 1, room = (int64_t)limit - 4096;
     p.vgroup = p.splits;
     p.bpanel = b;
     p.mpanel = m;
@@ -497,7 +691,7 @@ bool x3_panels(ApplyPlan& p, int64_t m, int64_t b, size_t limit) {
     p.part_bytes = (size_t)p.splits * p.bpanel * p.kpad * 4;
     p.mid_bytes = (size_t)p.bpanel * p.Kp * 4;
     p.stage_bytes = round_up((size_t)6 * p.bpanel * p.ldk, 256) + round_up((size_t)6 * p.mpanel * p.ldk, 256) +
-                    round_up((size_t)(vsplit * p.vgroup), 256);
+                    round_up((size_t)6 * p.kpad * p.chunk * p.vgroup, 256) + round_up((size_t)x3_mark_bytes(p), 256);
     return true;
 }
 
@@ -507,13 +701,17 @@ static hipError_t x3_apply(const ApplyPlan& p, const float* U, const float* s, c
     unsigned short* Tp = static_cast<unsigned short*>(ws.take((size_t)6 * p.bpanel * p.ldk));
     unsigned short* Up = static_cast<unsigned short*>(ws.take((size_t)6 * p.mpanel * p.ldk));
     unsigned short* Vp = static_cast<unsigned short*>(ws.take((size_t)6 * p.kpad * p.chunk * p.vgroup));
+    char* marks = static_cast<char*>(ws.take((size_t)x3_mark_bytes(p)));
     if (ws.overrun) return hipErrorOutOfMemory;
+    auto* umask = reinterpret_cast<unsigned long long*>(marks);
+    auto* tmask = reinterpret_cast<unsigned long long*>(marks + x3_umask_bytes(p));
+    auto* vflag = reinterpret_cast<unsigned char*>(tmask) + x3_tmask_bytes(p);
     // planes of `rows` rows of U and of `cols` rows of V (0: none)
     auto planes = [&](const float* u, int64_t rows, const float* v, int64_t cols, int64_t ldn) {
         KernelTimer t("apply_planes_f32", stream);
         const unsigned ub = (unsigned)((rows * (p.ldk / 8) + 255) / 256), nt = (unsigned)((ldn + 63) / 64);
         hipLaunchKernelGGL(k_x3_planes, dim3(ub + nt * (unsigned)((p.kpad + 63) / 64)), dim3(256), 0, stream, u, rows, k,
-                           Up, p.ldk, ub, v, cols, Vp, ldn, p.kpad, nt);
+                           Up, p.ldk, ub, v, cols, Vp, ldn, p.kpad, nt, umask, vflag);
     };
     const bool whole_u = p.mpanel >= m, whole_v = p.vgroup >= p.splits;
     const int vec16 = vec_ok<float>(Y, b) ? 1 : 0;
@@ -528,14 +726,14 @@ static hipError_t x3_apply(const ApplyPlan& p, const float* U, const float* s, c
             const dim3 g(xcd_grid((int64_t)p.tiles_m * tn * ns));
 #define LRC_P1X(NF)                                                                                                 \
     hipLaunchKernelGGL(k_p1_x3<NF>, g, dim3(256), 0, stream, Vp, ldn, p.kpad, V + r0 * k, k, X + r0 * b + b0, b, rows, \
-                       bw, p.chunk, p.nf, p.tiles_m, tn, (int)ns, part + s0 * bw * p.kpad)
+                       bw, p.chunk, p.nf, p.tiles_m, tn, (int)ns, vflag, part + s0 * bw * p.kpad)
             if (p.nf <= 5) LRC_P1X(5); else if (p.nf <= 9) LRC_P1X(9); else LRC_P1X(17);
 #undef LRC_P1X
         }
         {
             KernelTimer t("apply_p1_finish_f32", stream);
             hipLaunchKernelGGL(k_x3_finish, dim3((unsigned)((bw * (p.ldk / 4) + 255) / 256)), dim3(256), 0, stream,
-                               part, p.kpad, p.splits, s, k, bw, Tt, p.Kp, Tp, p.ldk);
+                               part, p.kpad, p.splits, s, k, bw, Tt, p.Kp, Tp, p.ldk, tmask);
         }
         for (int64_t m0 = 0; m0 < m; m0 += p.mpanel) {
             const int64_t mw = std::min(p.mpanel, m - m0);
@@ -543,7 +741,7 @@ static hipError_t x3_apply(const ApplyPlan& p, const float* U, const float* s, c
             KernelTimer t("apply_p2_mfma_f32", stream);
             const int tm = (int)((mw + 127) / 128);
             hipLaunchKernelGGL(k_p2_x3, dim3(xcd_grid(AbtOrder(tm, tn).total)), dim3(256), 0, stream, Up, Tp, p.ldk,
-                               U + m0 * k, mw, k, Tt, p.Kp, bw, tm, tn, Y + m0 * b + b0, b, vec16);
+                               U + m0 * k, mw, k, Tt, p.Kp, bw, tm, tn, umask, tmask, Y + m0 * b + b0, b, vec16);
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
