@@ -614,24 +614,37 @@ __global__ __launch_bounds__(256, 2) void k_p2_x3(const unsigned short* __restri
 constexpr int64_t kX3MaxChunk = (int64_t)64 * 32 * kX3BK;   // rows whose steps fit the bits of a wave's lanes
 constexpr int64_t kX3VBytes = (int64_t)16 << 20, kX3ColBytes = (int64_t)128 << 10;
 
-// Sizes that gain from the split (old and new times on the grid 512 <= m, n <=
-// 65536, k in {17, 41, 64, 129, 256, 512}, 128 <= b <= 8192): what it saves
-// grows with the (m + n) b values of X and Y, what it costs is the planes'
-// launch and 10 bytes per factor value.  From 32 M values on it gains 1.03 to
-// 1.9 times; between 16 M and 32 M 1.0 to 1.7 times, unless the rank is short
-// and every pitch aligned (k = 64: 0.86 to 0.94); from 7 M on only odd batches
-// (1.07 to 1.41 times: X needs no padded copy) and long odd ranks (1.06 to
-// 1.17); batches below 512 lose (0.5 to 0.9).
+// Sizes that gain from the split, times of the split over those of the FP32
+// instruction's plan beside each line (grids of 512 <= m, n <= 65536, 4 <= k <= 513, 512
+// <= b <= 8192).  What it saves grows with the (m + n) b values of X and Y and with
+// the rank; what it costs is the planes' launch and 10 bytes per factor value.
+// Odd batches gain by X read without a padded copy, odd ranks by U and V.
 static bool x3_takes(int64_t m, int64_t n, int64_t k, int64_t b, int prec, const void* U, const void* V,
                      const void* X) {
-    if (prec != P32 || b < 512 || m < 128) return false;
+    if (prec != P32 || b < 512 || m < 128) return false;   // batches below 512: 1.1 to 2
+    // Sums of up to three products: the terms that six products leave out (2.01
+    // 2^-24 of each) outweigh the roundings that they save (error of k = 1 in units
+    // of 2^-24 |U| |T'|: 4.2 against 2.6, k = 3 4.1 against 3.9, k = 4 3.7 against 4.4).
+    if (k < 4) return false;
     const int64_t kpad = round_up(k, 16) + 16 * 17;
     if ((double)n * kpad * 6.0 / kX3VBytes > (double)(kX3ColBytes / 4) / kpad) return false;
     const double values = (double)(m + n) * b;
     const bool xbad = needs_stage(X, b, prec), kbad = needs_stage(U, k, prec) || needs_stage(V, k, prec);
-    if (values >= 0x1p25) return b >= 1024 || k >= 96 || xbad || kbad;
-    if (values >= 0x1p24) return k >= 96 || xbad || kbad;
-    return values >= 7.0e6 && (xbad || (kbad && k >= 96));
+    const bool wide = n > 2 * m, tall = m > 2 * n;                // phase 1, bound by X, is the most or little of it
+    const bool xgain = xbad && !tall && values >= (b >= 1536 ? 7.0e6 : 8.0e6);   // 0.44 to 0.94; else 0.92 to 1.20
+    if (k <= 16) return xgain;                                    // else 1.0 to 1.23
+    if (values >= 0x1p25) {
+        if (k >= 96 || xbad) return true;                         // 0.47 to 1.02
+        if (kbad) return k > 32 || !wide;                         // 0.79 to 1.01; else 0.99 to 1.05
+        if (values < 0x1.2p25) return false;                      // 0.97 to 1.13
+        return !wide || (k > 32 && values >= 0x1p27);             // 0.76 to 1.01; else 0.97 to 1.13
+    }
+    // 0.52 to 1.0; else 0.72 to 1.18
+    if (values >= 0x1p24)
+        return xgain || k >= 160 || (k >= 96 && (kbad || b >= 1536)) || (kbad && b >= (tall ? 1536 : 2048));
+    // 0.76 to 0.97; else 0.84 to 1.20
+    const double least = tall ? 7.0e6 : k >= 160 ? 7.5e6 : 1.2e7;
+    return xgain || (kbad && k >= 96 && values >= least);
 }
 
 // Fragments per rank tile: at most 17, so that ranks 16 j + 1 (a compensated

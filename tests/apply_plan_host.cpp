@@ -4,6 +4,7 @@
 //            fits its scratch in the plan that runs
 //   memory   where only the memory of the plan without the split is free, the
 //            split's reservation still succeeds within it
+//   route    the FP32 split runs where it was measured to gain, not where it lost
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
@@ -67,8 +68,43 @@ void scratch(int64_t m, int64_t n, int64_t k, int64_t b) {
 }
 }  // namespace
 
+struct Route {
+    int64_t m, n, k, b;
+    bool split;
+};
+// times of the split over those of the FP32 instruction's plan beside each size
+const Route kRoutes[] = {
+    {8192, 8192, 257, 4096, true},    // 0.60
+    {2003, 1733, 41, 2047, true},     // 0.86
+    {65536, 4096, 513, 4096, true},   // 0.72
+    {4000, 30000, 16, 4095, true},    // 0.45
+    {2500, 2500, 24, 8192, true},     // 0.93
+    {8192, 8192, 129, 1024, true},    // 0.84
+    {11121, 25030, 16, 5440, false},  // 1.22
+    {30000, 4000, 8, 2048, false},    // 1.18
+    {4000, 30000, 24, 1024, false},   // 1.13
+    {2000, 16000, 41, 1024, false},   // 1.10
+    {16000, 1000, 41, 513, false},    // 1.19
+    {1200, 6000, 97, 1024, false},    // 1.16
+    {1200, 6000, 64, 1023, false},    // 1.10
+    {16384, 16384, 1, 4096, false},   // sums of three products and less: larger errors
+    {16384, 16384, 3, 4095, false},
+    {16384, 16384, 2, 8191, false},
+};
+
+void route(const Route& c) {
+    // factors of a rank that is no multiple of four and odd batches are misaligned by themselves
+    const void* p = reinterpret_cast<const void*>((uintptr_t)0x10000);
+    const ApplyPlan plan = plan_apply(c.m, c.n, c.k, c.b, P32, 0, p, p, p);
+    if ((plan.x3 != 0) != c.split) failed(c.m, c.n, c.k, c.b, plan.x3, c.split);
+}
+
 int main(int argc, char** argv) {
     if (argc != 2) return 3;
+    if (std::strcmp(argv[1], "route") == 0) {
+        for (const Route& c : kRoutes) route(c);
+        return bad ? 1 : 0;
+    }
     const auto check = std::strcmp(argv[1], "scratch") == 0 ? scratch : memory;
     // one split of the planes of V just above a quarter of the scratch
     check(8194, 47657, 332, 5388);

@@ -20,11 +20,11 @@ def build_host(tmp_path, source):
     return exe
 
 
-@pytest.mark.parametrize("sweep", ["scratch", "memory"])
+@pytest.mark.parametrize("sweep", ["scratch", "memory", "route"])
 def test_plans_fit(tmp_path, sweep):
     """Every FP32 call that the allocation-free entry accepts fits its scratch;
-    and every call still runs where only the memory of the plan without the
-    split is free."""
+    every call still runs where only the memory of the plan without the split is
+    free; and the split runs at the sizes and ranks where it gains."""
     r = subprocess.run([build_host(tmp_path, "apply_plan_host.cpp"), sweep], capture_output=True, text=True, timeout=300)
     print(r.stdout[-2000:])
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
