@@ -65,3 +65,16 @@ def test_measured_traffic_follows_the_source_hash(tmp_path, monkeypatch):
     assert bench.measured_traffic("tt_fused_f16") is None
     monkeypatch.setattr(bench, "kernel_source_hash", lambda: "0" * 16)
     assert bench.measured_traffic("apply_p2_mfma_f64") is None
+
+
+def test_split_fp32_products_are_priced_as_six():
+    # an FP32 apply whose operands were split into planes is bound by six
+    # bfloat16 products for one of its own, any other by the FP32 instruction
+    f, by = 1.0e12, 1.0e8
+    kern = {"apply_p1_mfma_f32": 1.0, "apply_p2_mfma_f32": 2.0}
+    plain = bench._record("apply", "apply", "f32", dict(kern), 3.0, f, by)
+    split = bench._record("apply", "apply", "f32", dict(kern, apply_planes_f32=0.1), 3.1, f, by)
+    assert np.isclose(plain["t_star_ms"], f / 157.3e12 * 1e3)
+    assert np.isclose(split["t_star_ms"], f / (2500.0e12 / 6) * 1e3)
+    assert bench.peak_tflops("f32", "tt_fused_f32", {"apply_planes_f32"}) == 157.3
+    assert bench.peak_tflops("f16", "apply_p2_mfma_f16", {"apply_planes_f32"}) == 2500.0
