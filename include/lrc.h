@@ -20,8 +20,9 @@
  *   Layout.  Dense, row-major (C order), no padding, every element in the
  *     storage precision `prec` unless stated otherwise.
  *   Precision codes.  LRC_FP64 = IEEE binary64 with binary64 accumulation;
- *     LRC_FP32 = binary32 with binary32 accumulation; LRC_FP16 = binary16
- *     storage with binary32 accumulation (the paper's protocol, Sec. 3.4).
+ *     LRC_FP32 = binary32 with binary32 accumulation (large applies: see
+ *     lrc_matrix_apply); LRC_FP16 = binary16 storage with binary32
+ *     accumulation (the paper's protocol, Sec. 3.4).
  *   Streams.  Work is enqueued on the calling thread's stream
  *     (lrc_set_stream, default the null stream).  lrc_matrix_apply and
  *     lrc_tt_reconstruct return without synchronizing; lrc_certify
@@ -91,6 +92,17 @@ extern "C" {
  * it is rounded once to binary16 as the input of the second product);
  * phase 2 forms Y = U T'.  Sums are split in a fixed order, so the result is
  * bitwise reproducible run to run.
+ * LRC_FP32 with batch >= 512, k >= 4 and large operands forms the products from
+ * exact splits of both operands into three bfloat16 values: six of the nine
+ * partial products, accumulated in binary32.  What is left out is at most
+ * 2.01 * 2^-24 |a b| per product a b; fewer roundings of the sums make up for
+ * it (measured errors against binary64 are 0.5 to 0.95 of those of the binary32
+ * instruction).  Values of U, V, X or T' that are neither 0 nor in
+ * [2^-100, 2^62), infinities and NaN among them, take the binary32 instruction
+ * with the up to 32 terms beside them, as does every sum that is not finite, so
+ * that subnormals, overflow and NaN come out as in binary32; time then depends
+ * on the values, up to 1.35 times that of the instruction throughout.  Such a
+ * call takes up to 1 GiB of workspace, and less where that is not free.
  * Errors: LRC_EINVAL if a pointer is NULL, m, n, k or batch < 1, k >
  * min(m, n), prec is unknown or Y overlaps an input; LRC_EOVERFLOW if an
  * element count overflows; LRC_ENOMEM / LRC_EHIP / LRC_ENODEV from the
@@ -113,9 +125,11 @@ int lrc_matrix_apply(const void* U, const void* s, const void* V, const void* X,
  * Every call on one device shares that device's array and leaves its last
  * contents there: calls that overlap in time on one device (two streams,
  * two threads) race on it and must be serialized by the caller.
- * Errors: those of lrc_matrix_apply, and LRC_EINVAL when the plan for these
- * sizes needs more than LRC_NOALLOC_SCRATCH_BYTES of scratch (checked on
- * the host before anything is launched).
+ * Errors: those of lrc_matrix_apply, and LRC_EINVAL when these sizes call for
+ * more than LRC_NOALLOC_SCRATCH_BYTES of scratch (checked on the host before
+ * anything is launched).  The limit counts T', the partial sums of unsplit
+ * products and padded copies of misaligned operands, whether or not the plan
+ * that would run takes that much.
  */
 #define LRC_NOALLOC_SCRATCH_BYTES (64LL << 20)
 int lrc_matrix_apply_noalloc(const void* U, const void* s, const void* V, const void* X, void* Y,

@@ -10,17 +10,23 @@
 // their own precision; FP16 accumulates in FP32 and rounds T' once to FP16
 // because it is the FP16 input of the second matrix-core product.
 //
-// Two kernel pairs (regime dispatch):
+// Kernels by size (plan_apply):
 //   streaming  batch <= 8: one lane per column of V (phase 1) and wavefront
 //              dot products with a butterfly reduction over rows of U
 //              (phase 2); the factors are read once, coalesced.
+//   one launch the smallest larger batches, both phases (apply_small.h).
 //   MFMA       otherwise: 128 x 128 (large shapes) or 64 x 64 output tiles
 //              on the 16x16 matrix cores (f64 16x16x4, f32 16x16x4, f16
 //              16x16x32 with FP32 accumulation); operands move in 16-byte
-//              chunks (operands with an unaligned pitch are first copied
-//              into a padded workspace), are staged through LDS with three
+//              chunks (operands with an unaligned pitch are read in place
+//              by shifted chunks or first copied into a padded workspace,
+//              whichever costs less), are staged through LDS with three
 //              K steps of loads in flight; workgroups are renumbered so
 //              that tiles sharing an operand run on the same XCD.
+//   FP16 phase 2 of large outputs: 256 x 128 tiles fed by direct LDS loads
+//              (apply_half.h).
+//   FP32 at large batches: both phases as six bfloat16 products of operands
+//              split into three parts (apply_split.h).
 #include <cstdlib>
 #include <type_traits>
 

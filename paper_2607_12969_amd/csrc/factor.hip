@@ -206,9 +206,10 @@ __device__ __forceinline__ bool jac_inside(JacCol<PER>& a, bool second, double t
 // rows of pitch ldw with zeros in columns l..ldw-1; s_out[pos] = sigma for
 // pos < k when not null.
 // Bound by the issue of one compute unit and the chain dot - rotation -
-// update of a step, about 8 (4 ceil(l / 8) + 1) steps; a round per column
-// pair, with IEEE divisions and a trip through LDS each, took 1006 us at l = 74,
-// this takes 601.
+// update of a step: a sweep is 8 ceil(l / 8) + 2 steps, and sketches with decaying
+// spectra take 7 (l = 16) to 9 sweeps.  A round per column pair, with IEEE
+// divisions and a trip through LDS each, took 1006 us at l = 74 (8 sweeps), this
+// takes 601.
 constexpr int kJacPitch = 104;   // doubles: four neighbouring columns fall on distinct banks
 constexpr int kJacThreads = 64 * (kFactMaxL / 8);
 static_assert(kFactMaxL % 16 == 0 && kFactMaxL <= kJacPitch, "blocks of the largest sketch");

@@ -358,7 +358,7 @@ int lrc_matrix_apply_noalloc(const void* U, const void* s, const void* V, const 
     const size_t need = plan.scratch_bytes;
     if (need > (size_t)LRC_NOALLOC_SCRATCH_BYTES ||
         (plan.x3 && !x3_panels(plan, m, batch, (size_t)LRC_NOALLOC_SCRATCH_BYTES)))
-        return fail(LRC_EINVAL, "this apply needs %zu bytes of scratch, above the %lld of the allocation-free entry",
+        return fail(LRC_EINVAL, "this apply is sized at %zu bytes of scratch, above the %lld of the allocation-free entry",
                     need, (long long)LRC_NOALLOC_SCRATCH_BYTES);
     int dev;
     rc = current_device(&dev, nullptr);

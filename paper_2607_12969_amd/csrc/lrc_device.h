@@ -35,7 +35,8 @@ template <> struct PrecTraits<double> {
     static constexpr int KB = 4;    // K per MFMA
 };
 
-// binary32 storage, binary32 accumulation: v_mfma_f32_16x16x4_f32
+// binary32 storage, binary32 accumulation: v_mfma_f32_16x16x4_f32 (large applies
+// take six bfloat16 products instead, apply_split.h)
 template <> struct PrecTraits<float> {
     using acc = float;
     using accv = float4_t;
