@@ -329,11 +329,11 @@ def hbm_ceilings(dev, gib=4):
 
 def kernel_source_hash():
     """Hash of the kernel sources and their launch plans (the .hip files and
-    the device header); host-only API code does not change HBM traffic."""
+    the headers); host-only API code does not change HBM traffic."""
     h = hashlib.sha256()
     d = os.path.join(ROOT, "paper_2607_12969_amd", "csrc")
     for f in sorted(os.listdir(d)):
-        if f.endswith(".hip") or f == "lrc_device.h":
+        if f.endswith((".hip", ".h")):
             with open(os.path.join(d, f), "rb") as fh:
                 h.update(fh.read())
     return h.hexdigest()[:16]

@@ -78,3 +78,17 @@ def test_split_fp32_products_are_priced_as_six():
     assert np.isclose(split["t_star_ms"], f / (2500.0e12 / 6) * 1e3)
     assert bench.peak_tflops("f32", "tt_fused_f32", {"apply_planes_f32"}) == 157.3
     assert bench.peak_tflops("f16", "apply_p2_mfma_f16", {"apply_planes_f32"}) == 2500.0
+
+
+def test_source_hash_covers_every_kernel_source(tmp_path, monkeypatch):
+    # counters must not outlive a change of any kernel source, headers included
+    import shutil
+    csrc = tmp_path / "paper_2607_12969_amd" / "csrc"
+    shutil.copytree(os.path.join(ROOT, "paper_2607_12969_amd", "csrc"), csrc)
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    kernels = [f for f in csrc.iterdir() if "__global__" in f.read_text() or "__device__ __forceinline__" in f.read_text()]
+    assert any(f.suffix == ".h" for f in kernels)
+    for f in kernels:
+        before = bench.kernel_source_hash()
+        f.write_text(f.read_text() + "\n// changed\n")
+        assert bench.kernel_source_hash() != before, f.name
