@@ -158,6 +158,7 @@ def _check(rc: int):
 # the current stream is read as a raw handle, without a Stream object
 # (0.1 against 2.3 us).
 _dtypes = None
+_plain = None
 _raw_stream = None
 
 
@@ -170,6 +171,18 @@ def _prec_of(t) -> int:
     if p is None:
         raise TypeError(f"unsupported dtype {t.dtype}")
     return p
+
+
+def _new(t, shape):
+    """An uninitialised plain tensor of t's dtype on its device."""
+    global _plain
+    if _plain is None:
+        import torch
+        _plain = torch.Tensor
+    if type(t) is _plain:
+        return t.new_empty(shape)            # 2 us less than torch.empty
+    import torch
+    return torch.empty(shape, dtype=t.dtype, device=t.device)   # new_empty would keep a subclass
 
 
 def _dev(*ts):
@@ -237,7 +250,7 @@ def matrix_apply(U, s, V, X, Y=None):
     _dev(U, s, V, X)
     dev = U.device
     if Y is None:
-        Y = U.new_empty((m, b))
+        Y = _new(U, (m, b))
     else:
         _dev(Y)
     _need(s.device == dev and V.device == dev and X.device == dev and Y.device == dev,
@@ -311,7 +324,7 @@ def tt_reconstruct(cores, out=None):
     _dev(*cores)
     dev = cores[0].device
     if out is None:
-        out = cores[0].new_empty(dims)
+        out = _new(cores[0], dims)
     else:
         _dev(out)
     for c in cores:

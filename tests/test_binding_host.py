@@ -93,3 +93,13 @@ def test_certify_tt_checks_trains():
 def test_mfma_ceiling_rejects_unknown_precision():
     with pytest.raises(ValueError, match="prec"):
         lrc.mfma_ceiling("bf16")
+
+
+def test_outputs_are_plain_tensors():
+    """An input of a tensor subclass does not pass its type on to the output."""
+    class Sub(torch.Tensor):
+        pass
+    for t in (torch.zeros(3, 2, dtype=torch.float16), torch.nn.Parameter(torch.zeros(3, 2)),
+              torch.zeros(3, 2).as_subclass(Sub)):
+        y = lrc._new(t, (4, 5))
+        assert type(y) is torch.Tensor and y.shape == (4, 5) and y.dtype == t.dtype and not y.requires_grad
