@@ -178,7 +178,7 @@ __global__ __launch_bounds__(256) void k_x3_planes(const float* __restrict__ U, 
 // in registers, so X is read and split once per rank tile and needs neither
 // copy nor LDS.  Two workgroups per compute unit cover each other's load
 // latency.  Bound by the matrix cores: 8192 x 8192, k = 257, b = 4096 runs in
-// 101 us against 201 us on the FP32 instruction (split operands of both
+// 96 us against 201 us on the FP32 instruction (split operands of both
 // sides through LDS, 64 rank rows per tile: 191 us).  A wave leaves out the
 // steps with a value outside the split's range and runs them after the loop on
 // the FP32 instruction.
@@ -423,8 +423,9 @@ __global__ __launch_bounds__(256) void k_x3_finish(const float* __restrict__ par
 // marked, or a mark among more than 64, or sums that are not finite, runs all
 // of them that way.
 // Bound by the matrix cores at the clock that their power leaves (1.6 to 1.8
-// of 2.4 GHz here): 65536 x 4096, k = 513, b = 4096 in 1370 to 1550 us against
-// 2160 us on the FP32 instruction; 8192 x 8192, k = 257 in 103 against 168 us.
+// of 2.4 GHz here): 65536 x 4096, k = 513, b = 4096 in 1540 to 1580 us against
+// 2160 us on the FP32 instruction; 8192 x 8192, k = 257 in 107 against 168 us
+// (reading the marks costs 2 % of it).
 // Measured before it: both operands split on their way to LDS 1650 us (the
 // splits' vector work), fragments read as they are used and three workgroups
 // per compute unit 1547 against 1366 us.
