@@ -96,7 +96,7 @@ extern "C" {
  * exact splits of both operands into three bfloat16 values: six of the nine
  * partial products, accumulated in binary32.  What is left out is at most
  * 2.01 * 2^-24 |a b| per product a b; fewer roundings of the sums make up for
- * it (measured errors against binary64 are 0.5 to 0.95 of those of the binary32
+ * it (measured errors against binary64 are 0.37 to 0.95 of those of the binary32
  * instruction).  Values of U, V, X or T' that are neither 0 nor in
  * [2^-100, 2^62), infinities and NaN among them, take the binary32 instruction
  * with the up to 32 terms beside them, as does every sum that is not finite, so
