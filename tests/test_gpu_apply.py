@@ -320,7 +320,7 @@ def test_fp32_split_panels_same_bits(lrc):
 
 @pytest.mark.parametrize("what", ["inf", "nan", "tiny", "huge"])
 def test_fp32_split_special_values(lrc, what):
-    """Values outside the split's range (2^-100 to 2^62): their tiles run on
+    """Values outside the split's range (2^-100 to 2^62): their K steps run on
     the FP32 instruction, so infinities and NaN land where the FP64 product
     has them, and tiny or huge columns keep the FP32 tolerance by themselves."""
     m, n, k, b = 1030, 1500, 70, 8200
